@@ -53,7 +53,7 @@ PROBE_LIB = os.path.join(HERE, "paper_2608_28113_amd", "libhscale_probes.so")
 # Sources of the hot-path kernels (hdiag, search): the committed HBM-traffic
 # figures are valid only for the source they were measured on.
 HOT_SOURCES = ("common.h", "hdiag.hip", "search.hip")
-DIAG_SOURCES = ("common.h", "diag.hip")
+DIAG_SOURCES = ("common.h", "gram.h", "diag.hip")
 
 
 def source_hash(names=HOT_SOURCES) -> str:

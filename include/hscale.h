@@ -363,10 +363,18 @@ size_t hscale_output_error_workspace_bytes(int64_t tokens, int64_t in,
  * accumulated into, so calibration batches streamed through successive
  * calls add up; zero it first.
  *
- * Arithmetic: dW is formed in fp32 with one rounding and split into two bf16
- * parts hi + lo (within 2^-18 |dW|); X dW^T is computed on the matrix cores
- * as bf16 products accumulated in fp32; squares and sums are fp64 in a fixed
- * order (bitwise reproducible for a given problem).
+ * Arithmetic: dW is formed in fp32 with one rounding.  The direct product
+ * splits it into two bf16 parts hi + lo (within 2^-18 |dW|) and computes
+ * X dW^T on the matrix cores as bf16 products accumulated in fp32; squares
+ * and sums are fp64 in a fixed order.  Where many output rows share a long X
+ * (a rule on the sizes) and the workspace holds what
+ * hscale_output_error_workspace_bytes says, the same sums come from
+ * G = X^T X instead: exact bf16 products accumulated in fp32 over token
+ * chunks, added in fp64; G's diagonal applied in fp64, the rest as 22-bit
+ * scaled values; rows whose terms cancel to below 1/16 of their diagonal
+ * part, or leave fp32's range, are computed by the direct product.  Both are
+ * bitwise reproducible for a given problem and workspace size; the second is
+ * the closer to Eq. 3 (about 1e-7 against 4e-6 of the result).
  *
  * X            bf16 [tokens, in], 16-byte aligned
  * W            bf16 [out, in], 16-byte aligned
@@ -377,7 +385,9 @@ size_t hscale_output_error_workspace_bytes(int64_t tokens, int64_t in,
  * row_err      fp64 [out], 8-byte aligned, in/out
  * workspace    >= hscale_output_error_workspace_bytes(tokens, in, out)
  *              bytes, 256-byte aligned, scratch owned by the caller (it holds
- *              the two dW planes and per-tile partial sums)
+ *              the two dW planes and per-tile partial sums, and for G its
+ *              partial tiles and two planes: at most 1.2 GB beside the
+ *              planes); one that holds only the direct product's is enough
  * in % 16 == 0 and in <= 2^21 (HSCALE_ERR_SHAPE beyond: the kernel
  * addresses a tile of X and of dW with 32-bit offsets); global_scale as
  * hscale_search.  tokens, in or out = 0 adds nothing.

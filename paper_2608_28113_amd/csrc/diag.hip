@@ -204,37 +204,55 @@ __device__ __forceinline__ uint32_t bf16_bits_rne(float f) {
     return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;  // finite inputs
 }
 
+// dW = w - v S of one group, one rounding per element.
+template <int K>
+__device__ __forceinline__ void delta_pair(const float (&w)[kGroup], uint32_t src, float S, float (&dw)[kGroup]) {
+    const auto v = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(src, 1.0f, K & 3);
+    dw[2 * K] = fmaf(-v[0], S, w[2 * K]);
+    dw[2 * K + 1] = fmaf(-v[1], S, w[2 * K + 1]);
+}
+
+__device__ __forceinline__ void delta_group(const float (&w)[kGroup], uint2 p, float S, float (&dw)[kGroup]) {
+    delta_pair<0>(w, p.x, S, dw);
+    delta_pair<1>(w, p.x, S, dw);
+    delta_pair<2>(w, p.x, S, dw);
+    delta_pair<3>(w, p.x, S, dw);
+    delta_pair<4>(w, p.y, S, dw);
+    delta_pair<5>(w, p.y, S, dw);
+    delta_pair<6>(w, p.y, S, dw);
+    delta_pair<7>(w, p.y, S, dw);
+}
+
 // dW of one 16-weight group, split into hi / lo bf16 planes of row stride
 // ldd; groups beyond (out, in) in the padded planes are written as zeros.
+// With a list, plane row r is weight row list[r], r < *count.
 __global__ __launch_bounds__(256) void delta_split_kernel(const u32x4 *__restrict__ W, int64_t out, int64_t in,
                                                           float s_g, const uint8_t *__restrict__ codes,
                                                           const uint2 *__restrict__ packed, int64_t rows_pad,
                                                           int64_t ldd, u32x4 *__restrict__ hi,
-                                                          u32x4 *__restrict__ lo) {
+                                                          u32x4 *__restrict__ lo,
+                                                          const uint32_t *__restrict__ count,
+                                                          const uint32_t *__restrict__ list) {
     const int64_t Gp = ldd / kGroup, Gc = in / kGroup;
+    if (list) {
+        out = *count;
+        rows_pad = (out + kLfBN - 1) / kLfBN * kLfBN;
+    }
     const int64_t total = rows_pad * Gp;
     const int64_t stride = (int64_t)gridDim.x * 256;
     for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < total; q += stride) {
         const int64_t r = q / Gp, i = q % Gp;
         uint32_t hb[8], lb[8];
         if (r < out && i < Gc) {
-            const int64_t g = r * Gc + i;
+            const int64_t g = (list ? (int64_t)list[r] : r) * Gc + i;
             float w[kGroup];
             load_group(W, g, w);
             const float S = s_g * e4m3fn_value(codes[g]);
-            const uint2 p = packed[g];
+            float dw[kGroup];
+            delta_group(w, packed[g], S, dw);
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
-                const uint32_t src = k < 4 ? p.x : p.y;
-                float2 v;
-                switch (k & 3) {
-                    case 0: { const auto t = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(src, 1.0f, 0); v = make_float2(t[0], t[1]); break; }
-                    case 1: { const auto t = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(src, 1.0f, 1); v = make_float2(t[0], t[1]); break; }
-                    case 2: { const auto t = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(src, 1.0f, 2); v = make_float2(t[0], t[1]); break; }
-                    default: { const auto t = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(src, 1.0f, 3); v = make_float2(t[0], t[1]); break; }
-                }
-                const float d0 = fmaf(-v.x, S, w[2 * k]);
-                const float d1 = fmaf(-v.y, S, w[2 * k + 1]);
+                const float d0 = dw[2 * k], d1 = dw[2 * k + 1];
                 const uint32_t h0 = bf16_bits_rne(d0), h1 = bf16_bits_rne(d1);
                 const uint32_t l0 = bf16_bits_rne(d0 - __uint_as_float(h0 << 16));
                 const uint32_t l1 = bf16_bits_rne(d1 - __uint_as_float(h1 << 16));
@@ -276,6 +294,7 @@ struct LfArgs {
     int64_t out;      // weight rows
     int64_t ntiles;   // rows_pad / kLfBN
     double *partial;  // [token tiles of the pass, out]
+    const uint32_t *count;  // lfull_listed_kernel: rows in the planes
 };
 
 // The (token tile, row tile) of block b.  Blocks are dispatched to the 8
@@ -305,13 +324,14 @@ __device__ __forceinline__ void lf_tile_of_block(int64_t b, int64_t total, int64
     }
 }
 
-__global__ __launch_bounds__(kLfThreads, kLfWaves / 4) void lfull_tile_kernel(const LfArgs a) {
-    __shared__ __attribute__((aligned(16))) uint8_t lds[kLfStages][kLfRows * 64];
+// Tile `block` of `total` = token tiles x ntiles, for planes of `rows` rows.
+__device__ __forceinline__ void lf_tile(const LfArgs &a, uint8_t (*lds)[kLfRows * 64], int64_t block, int64_t total,
+                                        int64_t ntiles, int64_t rows) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: LDS addresses in SGPRs
     const int wm = wave % kLfWM, wn = wave / kLfWM;
     int64_t mt, nt;
-    lf_tile_of_block(blockIdx.x, gridDim.x, a.ntiles, mt, nt);
+    lf_tile_of_block(block, total, ntiles, mt, nt);
     const int64_t t0 = mt * kLfBM, r0 = nt * kLfBN;
     const int stages = (int)(a.ldd / kLfBK);
 
@@ -431,7 +451,26 @@ __global__ __launch_bounds__(kLfThreads, kLfWaves / 4) void lfull_tile_kernel(co
         double v = red[tid];
 #pragma unroll
         for (int w = 1; w < kLfWM; ++w) v += red[w * kLfBN + tid];
-        if (col < a.out) a.partial[mt * a.out + col] = v;
+        if (col < rows) a.partial[mt * a.out + col] = v;
+    }
+}
+
+// One tile per block.
+__global__ __launch_bounds__(kLfThreads, kLfWaves / 4) void lfull_tile_kernel(const LfArgs a) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[kLfStages][kLfRows * 64];
+    lf_tile(a, lds, blockIdx.x, gridDim.x, a.ntiles, a.out);
+}
+
+// The tiles of a list of rows whose length only the device knows: a resident
+// grid walks them, and leaves at once when the list is empty.
+__global__ __launch_bounds__(kLfThreads, kLfWaves / 4) void lfull_listed_kernel(const LfArgs a) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[kLfStages][kLfRows * 64];
+    for (int b = blockIdx.x;; b += gridDim.x) {
+        const int rows = (int)*a.count, ntiles = (rows + kLfBN - 1) / kLfBN;  // read again: no registers held
+        const int total = (int)((a.tokens + kLfBM - 1) / kLfBM) * ntiles;
+        if (b >= total) break;
+        lf_tile(a, lds, b, total, ntiles, rows);
+        __syncthreads();  // the reduction's LDS before the next tile's loads
     }
 }
 
@@ -456,6 +495,68 @@ LfPlan lfull_plan(int64_t tokens, int64_t in, int64_t out) {
     p.partial_offset = 2 * p.plane_bytes;
     p.bytes = p.partial_offset + (size_t)p.tiles_per_pass * (size_t)out * sizeof(double);
     return p;
+}
+
+}  // namespace
+
+#include "gram.h"
+
+namespace {
+
+constexpr unsigned kListedBlocks = 256;  // one per CU
+
+// Enqueues the Gram route: every row's sum in row_err, or its number in the
+// list for the direct product that follows.
+int gram_run(const GramPlan &gp, const LfPlan &p, const u32x4 *X, int64_t tokens, int64_t in, const u32x4 *W,
+             int64_t out, float s_g, const uint8_t *codes, const uint2 *packed, double *row_err, uint8_t *ws,
+             hipStream_t stream) {
+    float4 *partial = reinterpret_cast<float4 *>(ws + gp.partial_offset);
+    uint8_t *planes = ws + gp.plane_offset;
+    double *diag = reinterpret_cast<double *>(ws + gp.diag_offset);
+    float *scale = reinterpret_cast<float *>(ws + gp.scale_offset);
+    GramRow *info = reinterpret_cast<GramRow *>(ws + gp.info_offset);
+    double *part = reinterpret_cast<double *>(ws + gp.part_offset);
+    uint32_t *count = reinterpret_cast<uint32_t *>(ws + gp.list_offset);
+    u32x4 *hi = reinterpret_cast<u32x4 *>(ws), *lo = reinterpret_cast<u32x4 *>(ws + p.plane_bytes);
+    for (int64_t c0 = 0; c0 < gp.chunks; c0 += gp.pass_chunks) {
+        const int64_t chunks = gp.chunks - c0 < gp.pass_chunks ? gp.chunks - c0 : gp.pass_chunks;
+        const int64_t t0 = c0 * gp.chunk;
+        GramArgs a;
+        a.X = X + t0 * (in / 8);
+        a.tokens = tokens - t0 < chunks * gp.chunk ? tokens - t0 : chunks * gp.chunk;
+        a.in = in;
+        a.chunk = gp.chunk;
+        a.tri = (int)gp.tri;
+        a.partial = partial;
+        hipLaunchKernelGGL(gram_kernel, dim3((unsigned)(chunks * gp.tri)), dim3(kGrThreads), 0, stream, a);
+        if (launch_status() != HSCALE_OK) return HSCALE_ERR_HIP;
+        hipLaunchKernelGGL(gram_diag, dim3((unsigned)gp.nt), dim3(kGrTile), 0, stream, partial, (int)gp.tri,
+                           (int)chunks, c0 == 0, diag, scale);
+        if (launch_status() != HSCALE_OK) return HSCALE_ERR_HIP;
+        hipLaunchKernelGGL(gram_reduce, dim3((unsigned)(gp.tri * (kGrUnitVecs / 256))), dim3(256), 0, stream, partial,
+                           (int)gp.tri, (int)chunks, c0 == 0, c0 + chunks == gp.chunks,
+                           reinterpret_cast<double4 *>(ws + gp.g64_offset), gp.ldg, diag,
+                           reinterpret_cast<uint2 *>(planes), reinterpret_cast<uint2 *>(planes + gp.plane_bytes));
+        if (launch_status() != HSCALE_OK) return HSCALE_ERR_HIP;
+    }
+    hipLaunchKernelGGL(gram_rows, dim3((unsigned)((out + 3) / 4)), dim3(256), 0, stream, W, out, in, s_g, codes, packed,
+                       diag, scale, (double)tokens, p.ldd, hi, lo, info, count);
+    if (launch_status() != HSCALE_OK) return HSCALE_ERR_HIP;
+    GramApplyArgs g;
+    g.g1 = reinterpret_cast<const u32x4 *>(planes);
+    g.g2 = reinterpret_cast<const u32x4 *>(planes + gp.plane_bytes);
+    g.hi = hi;
+    g.lo = lo;
+    g.ldg = gp.ldg;
+    g.ldd = p.ldd;
+    g.out = out;
+    g.ntiles = p.ntiles;
+    g.part = part;
+    hipLaunchKernelGGL(gram_apply, dim3((unsigned)(gp.nt * p.ntiles)), dim3(kGrThreads), 0, stream, g);
+    if (launch_status() != HSCALE_OK) return HSCALE_ERR_HIP;
+    hipLaunchKernelGGL(gram_finish, dim3((unsigned)((out + 255) / 256)), dim3(256), 0, stream, info, part, (int)gp.nt,
+                       out, row_err, count, count + 64);
+    return launch_status();
 }
 
 int64_t summary_blocks(int64_t groups) { return groups > 0 ? (groups + kSumChunk - 1) / kSumChunk : 0; }
@@ -517,7 +618,9 @@ int hscale_shift_summary(const int8_t *shift, const float *err_best, const float
 
 size_t hscale_output_error_workspace_bytes(int64_t tokens, int64_t in, int64_t out) {
     if (in % kGroup != 0 || in > kLfMaxIn || (in > 0 && out > kMaxGroups / (in / kGroup))) return 0;
-    return lfull_plan(tokens, in, out).bytes;
+    const LfPlan p = lfull_plan(tokens, in, out);
+    const GramPlan g = gram_plan(tokens, in, out, p.ldd, p.rows_pad, p.bytes);
+    return g.use ? g.bytes : p.bytes;
 }
 
 int hscale_output_error(const void *X, int64_t tokens, int64_t in, const void *W, int64_t out, float global_scale,
@@ -544,13 +647,30 @@ int hscale_output_error(const void *X, int64_t tokens, int64_t in, const void *W
     for (const auto &b : ins)
         if (overlaps(row_err, nr, b.p, b.n) || overlaps(workspace, p.bytes, b.p, b.n)) return HSCALE_ERR_OVERLAP;
     if (overlaps(row_err, nr, workspace, p.bytes)) return HSCALE_ERR_OVERLAP;
+    // The Gram route needs more scratch than the direct one; a smaller
+    // workspace, or one whose further part overlaps a buffer, goes direct.
+    const GramPlan gp = gram_plan(tokens, in, out, p.ldd, p.rows_pad, p.bytes);
+    bool gram = gp.use && workspace_bytes >= gp.bytes && !overlaps(row_err, nr, workspace, gp.bytes);
+    for (const auto &b : ins) gram = gram && !overlaps(workspace, gp.bytes, b.p, b.n);
 
     uint8_t *ws = static_cast<uint8_t *>(workspace);
     u32x4 *hi = reinterpret_cast<u32x4 *>(ws), *lo = reinterpret_cast<u32x4 *>(ws + p.plane_bytes);
     double *partial = reinterpret_cast<double *>(ws + p.partial_offset);
-    hipLaunchKernelGGL(delta_split_kernel, dim3(grid_for(p.rows_pad * (p.ldd / kGroup), 256)), dim3(256), 0, stream,
-                       static_cast<const u32x4 *>(W), out, in, global_scale, scale_codes,
-                       reinterpret_cast<const uint2 *>(packed_e2m1), p.rows_pad, p.ldd, hi, lo);
+    const uint32_t *count = nullptr, *list = nullptr;
+    if (gram) {
+        const int status = gram_run(gp, p, static_cast<const u32x4 *>(X), tokens, in, static_cast<const u32x4 *>(W),
+                                    out, global_scale, scale_codes, reinterpret_cast<const uint2 *>(packed_e2m1),
+                                    row_err, ws, stream);
+        if (status != HSCALE_OK) return status;
+        count = reinterpret_cast<const uint32_t *>(ws + gp.list_offset);
+        list = count + 64;
+    }
+    // The direct product: of every row, or of the rows the Gram route listed
+    // (usually none), whose planes then take the place of the Gram route's.
+    const int64_t split_groups = p.rows_pad * (p.ldd / kGroup);
+    hipLaunchKernelGGL(delta_split_kernel, dim3(gram ? kListedBlocks : grid_for(split_groups, 256)), dim3(256), 0,
+                       stream, static_cast<const u32x4 *>(W), out, in, global_scale, scale_codes,
+                       reinterpret_cast<const uint2 *>(packed_e2m1), p.rows_pad, p.ldd, hi, lo, count, list);
     if (launch_status() != HSCALE_OK) return HSCALE_ERR_HIP;
     const int64_t pass_tokens = p.tiles_per_pass * kLfBM;
     for (int64_t t0 = 0; t0 < tokens; t0 += pass_tokens) {
@@ -564,10 +684,18 @@ int hscale_output_error(const void *X, int64_t tokens, int64_t in, const void *W
         a.out = out;
         a.ntiles = p.ntiles;
         a.partial = partial;
+        a.count = count;
         const int64_t tiles = (a.tokens + kLfBM - 1) / kLfBM;
-        hipLaunchKernelGGL(lfull_tile_kernel, dim3((unsigned)(tiles * p.ntiles)), dim3(kLfThreads), 0, stream, a);
+        if (gram)
+            hipLaunchKernelGGL(lfull_listed_kernel, dim3(kListedBlocks), dim3(kLfThreads), 0, stream, a);
+        else
+            hipLaunchKernelGGL(lfull_tile_kernel, dim3((unsigned)(tiles * p.ntiles)), dim3(kLfThreads), 0, stream, a);
         if (launch_status() != HSCALE_OK) return HSCALE_ERR_HIP;
-        launch_tree<true>(partial, tiles, out, nullptr, row_err, stream);
+        if (gram)
+            hipLaunchKernelGGL(gram_fallback, dim3((unsigned)((out + 255) / 256)), dim3(256), 0, stream, partial, tiles,
+                               out, count, list, row_err);
+        else
+            launch_tree<true>(partial, tiles, out, nullptr, row_err, stream);
         if (launch_status() != HSCALE_OK) return HSCALE_ERR_HIP;
     }
     return HSCALE_OK;

@@ -1,0 +1,149 @@
+"""The Gram route of hscale_output_error (many output rows on one X) against
+the direct route on the same inputs and against float64.
+
+The route is chosen from the sizes and from the workspace: a workspace of the
+direct route's size keeps the direct product, which gives both on one input.
+"""
+from __future__ import annotations
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def hs():
+    import paper_2608_28113_amd as hs
+    assert torch.cuda.is_available()
+    return hs
+
+
+def _direct_bytes(T, n, m):
+    """Workspace of the direct route: two padded bf16 planes of dW and fp64
+    partials of at most 1024 token tiles of 384."""
+    ldd, rows = -(-n // 32) * 32, -(-m // 256) * 256
+    plane = -(-rows * ldd * 2 // 256) * 256
+    return 2 * plane + min(-(-T // 384), 1024) * m * 8
+
+
+def _case(T, n, m, seed):
+    """Activations with shared directions and outlier channels, weights with
+    any stored codes near their max-abs ones, and dW in float64."""
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    sigma = torch.exp(0.6 * torch.randn(n, generator=g, device=DEV))
+    sigma[:: max(1, n // 3)] *= 50.0
+    mix = 0.3 * torch.randn((4, n), generator=g, device=DEV)
+    X = torch.empty((T, n), dtype=torch.bfloat16, device=DEV)
+    for t in range(0, T, 16384):
+        k = min(16384, T - t)
+        z = torch.randn((k, n), generator=g, device=DEV)
+        X[t:t + k] = (z + torch.randn((k, 4), generator=g, device=DEV) @ mix) * sigma
+    W = (0.02 * torch.randn((m, n), generator=g, device=DEV)).to(torch.bfloat16)
+    return X, W
+
+
+def _stored(hs, W):
+    h = torch.ones(W.shape[1], device=DEV)
+    s_g = float((W.abs().max().float() / 2688.0).item())
+    codes, packed = hs.search(W, h, s_g, window=2)
+    return s_g, codes, packed
+
+
+def _reference(X, W, s_g, codes, packed):
+    """Eq. 3 per row in float64 torch."""
+    m, n = W.shape
+    grid = torch.tensor([s * v for s in (1.0, -1.0) for v in (0, 0.5, 1, 1.5, 2, 3, 4, 6)], dtype=torch.float64,
+                        device=DEV)
+    S = (codes.view(torch.float8_e4m3fn).float() * torch.tensor(s_g, device=DEV)).double()
+    q = torch.stack([packed & 15, packed >> 4], -1).view(m, n)
+    dW = W.double() - (grid[q.long()].view(m, n // 16, 16) * S[..., None]).view(m, n)
+    dW = dW.t().contiguous()
+    out = torch.zeros(m, dtype=torch.float64, device=DEV)
+    for t in range(0, X.shape[0], 16384):
+        out += (X[t:t + 16384].double() @ dW).square_().sum(0)
+    return out
+
+
+def _both(hs, X, W, s_g, codes, packed):
+    T, n = X.shape
+    m = W.shape[0]
+    need, direct = hs.output_error_workspace_bytes(T, n, m), _direct_bytes(T, n, m)
+    assert need > direct, "the sizes no longer take the Gram route"
+    print(f"[gram {T}x{n}x{m}] workspace {need} direct {direct}", flush=True)
+    gram = hs.output_error(X, W, s_g, codes, packed)
+    ws = torch.empty(direct, dtype=torch.uint8, device=DEV)
+    plain = hs.output_error(X, W, s_g, codes, packed, workspace=ws)
+    torch.cuda.synchronize()
+    return gram, plain
+
+
+def _rel(a, ref):
+    return ((a - ref).abs() / ref).max().item()
+
+
+# The direct route's bar (tests/test_gpu_diag.py): dW in two bf16 parts,
+# 2^-18 per element, rows of few dominant channels included.  The Gram route
+# takes the diagonal in fp64 and meets the same bar.
+REL_TOL = 1e-4
+
+
+# One column tile and a ragged one; a last tile of 16 columns; ragged tokens
+# and rows; more partial tiles than one pass holds (34 chunks x 136 tiles).
+@pytest.mark.parametrize("T,n,m", [(400001, 240, 4097), (120000, 528, 3000), (70007, 1040, 4100),
+                                   (65536, 2048, 2048), (8192 * 34 + 77, 4096, 4096)])
+def test_gram_route_matches_float64_and_the_direct_route(hs, T, n, m):
+    X, W = _case(T, n, m, seed=T + n + m)
+    s_g, codes, packed = _stored(hs, W)
+    codes[m // 2].zero_()  # a zero scale: dW = W
+    gram, plain = _both(hs, X, W, s_g, codes, packed)
+    ref = _reference(X, W, s_g, codes, packed)
+    norm = [((v - ref).norm() / ref.norm()).item() for v in (gram, plain)]
+    print(f"  max rel gram {_rel(gram, ref):.2e} direct {_rel(plain, ref):.2e}; norm {norm[0]:.2e} {norm[1]:.2e}",
+          flush=True)
+    assert torch.isfinite(gram).all() and _rel(gram, ref) <= REL_TOL
+    assert norm[0] <= norm[1] + 1e-6  # no precision lost against the direct product
+    again = hs.output_error(X, W, s_g, codes, packed, row_err=gram.clone())
+    torch.cuda.synchronize()
+    assert torch.equal(again, gram + gram)  # accumulates, and is repeatable bit for bit
+
+
+def _opposed(T, n, m, noise):
+    """Neighbouring channels nearly opposite; equal weights in even rows (y
+    cancels to about noise^2 / 2 of its diagonal part) and opposite ones in
+    odd rows (y adds up)."""
+    X, W = _case(T, n, m, seed=5)
+    g = torch.Generator(device=DEV).manual_seed(1)
+    X[:, 1::2] = -X[:, 0::2] * (1.0 + noise * torch.randn((T, n // 2), device=DEV, generator=g))
+    W[0::2, 1::2] = W[0::2, 0::2]
+    W[1::2, 1::2] = -W[1::2, 0::2]
+    return X, W
+
+
+@pytest.mark.parametrize("noise", [0.02, 0.1, 0.2, 0.4])
+def test_cancelling_rows_lose_no_precision(hs, noise):
+    """Rows on both sides of the line below which the direct product takes
+    over (up to 0.2 the even rows lie below it)."""
+    X, W = _opposed(65536, 1024, 4100, noise)
+    s_g, codes, packed = _stored(hs, W)
+    gram, plain = _both(hs, X, W, s_g, codes, packed)
+    ref = _reference(X, W, s_g, codes, packed)
+    for rows in (slice(0, None, 2), slice(1, None, 2)):
+        print(f"  noise {noise} max rel gram {_rel(gram[rows], ref[rows]):.2e} direct "
+              f"{_rel(plain[rows], ref[rows]):.2e}", flush=True)
+        assert _rel(gram[rows], ref[rows]) <= max(REL_TOL, 1.5 * _rel(plain[rows], ref[rows]))
+    if noise <= 0.2:
+        even = slice(0, None, 2)
+        assert ((gram[even] - plain[even]).abs() <= 1e-12 * plain[even]).all()  # the direct sums, in another order
+
+
+@pytest.mark.parametrize("scale", [2.0 ** -60, 2.0 ** 70])
+def test_squares_outside_fp32_go_direct(hs, scale):
+    X, W = _case(65536, 1024, 4096, seed=6)
+    X = X.mul_(scale)
+    s_g, codes, packed = _stored(hs, W)
+    gram, plain = _both(hs, X, W, s_g, codes, packed)
+    assert torch.isfinite(gram).all()
+    assert ((gram - plain).abs() <= 1e-12 * plain).all()
