@@ -160,7 +160,7 @@ __global__ __launch_bounds__(64) void shift_summary_final(const double *__restri
 // row r, with dW = W - W^ the rounding error of a stored NVFP4 tensor.
 //
 // dW is formed once in fp32 (w - v S[c], one rounding) and split into two
-// bf16 planes hi + lo (|dW - hi - lo| <= 2^-18 |dW|), so X dW^T is two bf16
+// bf16 planes hi + lo (|dW - hi - lo| <= 2^-16 |dW|), so X dW^T is two bf16
 // MFMA products accumulated in fp32.  Each block computes a 384-token x
 // 256-row tile of X dW^T in registers and reduces the squares of its columns
 // in fp64; the tile is never written.  Per-tile column sums go to a
@@ -284,6 +284,29 @@ __device__ __forceinline__ int lf_lds_offset(int row, int chunk) {
 // s_waitcnt immediate (gfx9 encoding) waiting until at most n vector memory
 // operations of this wave are outstanding; the other counters are left free.
 constexpr int waitcnt_vm(int n) { return (n & 0xF) | ((n >> 4) << 14) | (0x7 << 4) | (0xF << 8); }
+
+// Raw buffer descriptor of `bytes` bytes at a wave-uniform address.
+__device__ __forceinline__ u32x4 raw_descriptor(const void *p, uint32_t bytes) {
+    const uint64_t a = reinterpret_cast<uintptr_t>(p);
+    return u32x4{(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a),
+                 (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32) & 0xFFFF),
+                 (uint32_t)__builtin_amdgcn_readfirstlane((int)bytes), kRawBufferWord3};
+}
+
+// Starts a copy of 16 bytes per lane from the buffer to LDS at `dst` + 16 x
+// lane; the caller waits for vmcnt.  In assembly because the compiler, which
+// cannot tell the buffer being filled from the one being read, puts a wait
+// for the builtin's copies before LDS reads.  It writes no register but M0,
+// which nothing else in these kernels uses.
+__device__ __forceinline__ void load_to_lds(u32x4 rsrc, uint32_t offset, uint32_t dst) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 :
+                 : "s"(dst), "v"(offset), "s"(rsrc)
+                 : "memory");
+}
+
+constexpr int kWaitAll = 0x70;  // s_waitcnt vmcnt(0) lgkmcnt(0)
+constexpr int kSchedMfma = 0x008, kSchedLdsRead = 0x100;  // instruction classes of the scheduling groups
 
 struct LfArgs {
     const u32x4 *X;      // [tokens, in] bf16
@@ -474,9 +497,146 @@ __global__ __launch_bounds__(kLfThreads, kLfWaves / 4) void lfull_listed_kernel(
     }
 }
 
+// A tile of 128 tokens x 256 weight rows for problems of few tiles: 2 x 4
+// waves of 64 x 64, two per SIMD.  One wave's tile takes 6 LDS reads per 8
+// MFMAs, so it gives up a third of the rate of the large tile (0.56 of its
+// time for a third of its work); at 2048 tokens x 4096 x 4096 its 256 blocks
+// fill the chip where the large tile's 96 do not: 132 us against 234 us.
+constexpr int kLnBM = 128;
+constexpr int kLnWM = 2;
+constexpr int kLnThreads = 64 * kLnWM * kLfWN;
+constexpr int kLnRows = kLnBM + 2 * kLfBN;
+constexpr int kLnMI = kLnBM / kLnWM / 32;
+constexpr int kLnLoads = kLnRows / 16 / (kLnThreads / 64);  // 1 KB loads per wave and stage: X, hi (2), lo (2)
+static_assert(kLnLoads == 5 && kLnBM == 128, "wave w loads rows 16 w + 128 i of the stage");
+
+__global__ __launch_bounds__(kLnThreads, 2) void lfull_narrow_kernel(const LfArgs a) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[2][kLnRows * 64];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: LDS addresses in SGPRs
+    const int wm = wave % kLnWM, wn = wave / kLnWM;
+    int64_t mt, nt;
+    lf_tile_of_block(blockIdx.x, gridDim.x, a.ntiles, mt, nt);
+    const int64_t t0 = mt * kLnBM, r0 = nt * kLfBN;
+    const int stages = (int)(a.ldd / kLfBK);
+
+    // Loads and LDS layout as in lf_tile, except that the per-lane offsets
+    // advance by 64 bytes a stage.
+    const int64_t xrow_bytes = a.in * 2, drow_bytes = a.ldd * 2;
+    const int64_t valid_rows = a.tokens - t0 < kLnBM ? a.tokens - t0 : kLnBM;
+    const u32x4 rx = raw_descriptor(a.X + t0 * (a.in / 8), (uint32_t)(valid_rows * xrow_bytes));
+    const u32x4 rd[2] = {raw_descriptor(a.hi + r0 * (a.ldd / 8), (uint32_t)(kLfBN * drow_bytes)),
+                         raw_descriptor(a.lo + r0 * (a.ldd / 8), (uint32_t)(kLfBN * drow_bytes))};
+    const int row0 = wave * 16 + (lane >> 2);
+    const int c0 = (lane & 3) ^ ((row0 >> 2) & 3);
+    uint32_t vx = (uint32_t)(row0 * xrow_bytes + c0 * 16);
+    uint32_t vd[2] = {(uint32_t)(row0 * drow_bytes + c0 * 16), (uint32_t)((row0 + 128) * drow_bytes + c0 * 16)};
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds[0] + wave * 1024;
+    auto issue = [&](int buf) {
+        const uint32_t dst = lds0 + buf * (kLnRows * 64);
+        load_to_lds(rx, vx, dst);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) load_to_lds(rd[i >> 1], vd[i & 1], dst + (i + 1) * 8192);
+        vx += 64, vd[0] += 64, vd[1] += 64;
+    };
+
+    f32x16 acc[kLnMI][kLfNJ];
+#pragma unroll
+    for (int i = 0; i < kLnMI; ++i)
+#pragma unroll
+        for (int j = 0; j < kLfNJ; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+
+    // Two buffers, and two sets of operand registers: each 16-deep step's
+    // operands are read while the step before it multiplies, across stages
+    // too.  At a stage's last step its operands are in registers, so after
+    // the waits (own reads done, own copies of the next stage landed) and the
+    // barrier the buffer takes the stage after next, which then has a whole
+    // stage's time to arrive.
+    bf16x8 fa[2][kLnMI], fh[2][kLfNJ], fl[2][kLfNJ];
+    auto read_step = [&](const uint8_t *buf, int kk) {
+        const int c = 2 * kk + (lane >> 5);
+#pragma unroll
+        for (int i = 0; i < kLnMI; ++i)
+            fa[kk][i] = *reinterpret_cast<const bf16x8 *>(
+                buf + lf_lds_offset(wm * (kLnBM / kLnWM) + i * 32 + (lane & 31), c));
+#pragma unroll
+        for (int j = 0; j < kLfNJ; ++j) {
+            const int row = kLnBM + wn * (kLfBN / kLfWN) + j * 32 + (lane & 31);
+            fh[kk][j] = *reinterpret_cast<const bf16x8 *>(buf + lf_lds_offset(row, c));
+            fl[kk][j] = *reinterpret_cast<const bf16x8 *>(buf + lf_lds_offset(row + kLfBN, c));
+        }
+    };
+    issue(0);
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+    if (stages > 1) issue(1);
+    read_step(lds[0], 0);
+    for (int s = 0; s < stages; ++s) {
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            if (kk == 0) {
+                read_step(lds[s & 1], 1);
+            } else {
+                __builtin_amdgcn_s_waitcnt(kWaitAll);
+                asm volatile("s_barrier" ::: "memory");
+                if (s + 2 < stages) issue(s & 1);
+                read_step(lds[(s + 1) & 1], 0);
+            }
+#pragma unroll
+            for (int i = 0; i < kLnMI; ++i)
+#pragma unroll
+                for (int j = 0; j < kLfNJ; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kk][i], fh[kk][j], acc[i][j], 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < kLnMI; ++i)
+#pragma unroll
+                for (int j = 0; j < kLfNJ; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kk][i], fl[kk][j], acc[i][j], 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                __builtin_amdgcn_sched_group_barrier(kSchedMfma, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(kSchedLdsRead, 1, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    __syncthreads();
+
+    // Column sums of squares: lane l holds column l % 32 of each 32x32
+    // accumulator; lanes l and l + 32 share a column, and the kLnWM waves of
+    // a column group share its columns (added in wm order).
+    double sq[kLfNJ];
+#pragma unroll
+    for (int j = 0; j < kLfNJ; ++j) {
+        double v = 0.0;
+#pragma unroll
+        for (int i = 0; i < kLnMI; ++i)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const double y = (double)acc[i][j][e];
+                v = fma(y, y, v);
+            }
+        sq[j] = v + __shfl_xor(v, 32, 64);
+    }
+    double *red = reinterpret_cast<double *>(lds[0]);  // [kLnWM][kLfBN]
+    if (lane < 32) {
+#pragma unroll
+        for (int j = 0; j < kLfNJ; ++j) red[wm * kLfBN + wn * (kLfBN / kLfWN) + j * 32 + lane] = sq[j];
+    }
+    __syncthreads();
+    if (tid < kLfBN) {
+        const int64_t col = r0 + tid;
+        if (col < a.out) a.partial[mt * a.out + col] = red[tid] + red[kLfBN + tid];
+    }
+}
+
 struct LfPlan {
-    int64_t ldd = 0, rows_pad = 0, ntiles = 0, tiles_per_pass = 0;
-    size_t plane_bytes = 0, partial_offset = 0, bytes = 0;
+    int64_t ldd = 0, rows_pad = 0, ntiles = 0;
+    int64_t tile_tokens = 0;      // kLfBM or kLnBM
+    int64_t tiles_per_pass = 0;   // token tiles of a pass
+    size_t plane_bytes = 0, partial_offset = 0;
+    size_t least = 0, bytes = 0;  // smallest workspace accepted, and the one asked for
 };
 
 LfPlan lfull_plan(int64_t tokens, int64_t in, int64_t out) {
@@ -485,7 +645,12 @@ LfPlan lfull_plan(int64_t tokens, int64_t in, int64_t out) {
     p.ldd = (in + kLfBK - 1) / kLfBK * kLfBK;
     p.rows_pad = (out + kLfBN - 1) / kLfBN * kLfBN;
     p.ntiles = p.rows_pad / kLfBN;
-    const int64_t tiles = (tokens + kLfBM - 1) / kLfBM;
+    // The large tile, or the narrow one where it fills the 256 CUs in fewer
+    // rounds by more than its lower rate costs (0.56 of the time for a round).
+    const int64_t wide = (tokens + kLfBM - 1) / kLfBM, narrow = (tokens + kLnBM - 1) / kLnBM;
+    const int64_t wide_rounds = (wide * p.ntiles + 255) / 256, narrow_rounds = (narrow * p.ntiles + 255) / 256;
+    p.tile_tokens = 0.56 * (double)narrow_rounds < (double)wide_rounds ? kLnBM : kLfBM;
+    const int64_t tiles = p.tile_tokens == kLnBM ? narrow : wide;
     // A pass launches tiles_per_pass x ntiles blocks: at most kLfMaxTilesPerPass
     // token tiles, and never more blocks than a grid dimension holds.
     const int64_t grid_cap = INT_MAX / p.ntiles > 0 ? INT_MAX / p.ntiles : 1;
@@ -494,6 +659,9 @@ LfPlan lfull_plan(int64_t tokens, int64_t in, int64_t out) {
     p.plane_bytes = round_up((size_t)p.rows_pad * (size_t)p.ldd * 2, 256);
     p.partial_offset = 2 * p.plane_bytes;
     p.bytes = p.partial_offset + (size_t)p.tiles_per_pass * (size_t)out * sizeof(double);
+    // The partials of large tiles are enough: the narrow ones then take more
+    // passes.
+    p.least = p.partial_offset + (size_t)(wide < cap ? wide : cap) * (size_t)out * sizeof(double);
     return p;
 }
 
@@ -636,7 +804,7 @@ int hscale_output_error(const void *X, int64_t tokens, int64_t in, const void *W
         !aligned(workspace, 256))
         return HSCALE_ERR_ALIGN;
     const LfPlan p = lfull_plan(tokens, in, out);
-    if (workspace_bytes < p.bytes) return HSCALE_ERR_WORKSPACE;
+    if (workspace_bytes < p.least) return HSCALE_ERR_WORKSPACE;
     const size_t nx = (size_t)tokens * (size_t)in * 2, nw = (size_t)out * (size_t)in * 2;
     const size_t nc = (size_t)out * (size_t)(in / kGroup), np = (size_t)out * (size_t)(in / 2);
     const size_t nr = (size_t)out * 8;
@@ -645,13 +813,20 @@ int hscale_output_error(const void *X, int64_t tokens, int64_t in, const void *W
         size_t n;
     } ins[] = {{X, nx}, {W, nw}, {scale_codes, nc}, {packed_e2m1, np}};
     for (const auto &b : ins)
-        if (overlaps(row_err, nr, b.p, b.n) || overlaps(workspace, p.bytes, b.p, b.n)) return HSCALE_ERR_OVERLAP;
-    if (overlaps(row_err, nr, workspace, p.bytes)) return HSCALE_ERR_OVERLAP;
-    // The Gram route needs more scratch than the direct one; a smaller
-    // workspace, or one whose further part overlaps a buffer, goes direct.
+        if (overlaps(row_err, nr, b.p, b.n)) return HSCALE_ERR_OVERLAP;
+    auto hits = [&](size_t bytes) {  // the workspace's first bytes against every buffer
+        bool hit = overlaps(row_err, nr, workspace, bytes);
+        for (const auto &b : ins) hit = hit || overlaps(workspace, bytes, b.p, b.n);
+        return hit;
+    };
+    if (hits(p.least)) return HSCALE_ERR_OVERLAP;
+    // What a larger workspace adds is used where it is there and overlaps no
+    // buffer: the partials of the direct product's tiles in fewer passes, and
+    // the Gram route.
+    size_t direct_bytes = workspace_bytes < p.bytes ? workspace_bytes : p.bytes;
+    if (hits(direct_bytes)) direct_bytes = p.least;
     const GramPlan gp = gram_plan(tokens, in, out, p.ldd, p.rows_pad, p.bytes);
-    bool gram = gp.use && workspace_bytes >= gp.bytes && !overlaps(row_err, nr, workspace, gp.bytes);
-    for (const auto &b : ins) gram = gram && !overlaps(workspace, gp.bytes, b.p, b.n);
+    const bool gram = gp.use && workspace_bytes >= gp.bytes && !hits(gp.bytes);
 
     uint8_t *ws = static_cast<uint8_t *>(workspace);
     u32x4 *hi = reinterpret_cast<u32x4 *>(ws), *lo = reinterpret_cast<u32x4 *>(ws + p.plane_bytes);
@@ -672,7 +847,10 @@ int hscale_output_error(const void *X, int64_t tokens, int64_t in, const void *W
                        stream, static_cast<const u32x4 *>(W), out, in, global_scale, scale_codes,
                        reinterpret_cast<const uint2 *>(packed_e2m1), p.rows_pad, p.ldd, hi, lo, count, list);
     if (launch_status() != HSCALE_OK) return HSCALE_ERR_HIP;
-    const int64_t pass_tokens = p.tiles_per_pass * kLfBM;
+    const int64_t tile_tokens = gram ? kLfBM : p.tile_tokens;
+    int64_t pass_tiles = (int64_t)((direct_bytes - p.partial_offset) / ((size_t)out * sizeof(double)));
+    if (pass_tiles > p.tiles_per_pass) pass_tiles = p.tiles_per_pass;
+    const int64_t pass_tokens = pass_tiles * tile_tokens;
     for (int64_t t0 = 0; t0 < tokens; t0 += pass_tokens) {
         LfArgs a;
         a.tokens = tokens - t0 < pass_tokens ? tokens - t0 : pass_tokens;
@@ -685,11 +863,14 @@ int hscale_output_error(const void *X, int64_t tokens, int64_t in, const void *W
         a.ntiles = p.ntiles;
         a.partial = partial;
         a.count = count;
-        const int64_t tiles = (a.tokens + kLfBM - 1) / kLfBM;
+        const int64_t tiles = (a.tokens + tile_tokens - 1) / tile_tokens;
+        const dim3 grid((unsigned)(tiles * p.ntiles));
         if (gram)
             hipLaunchKernelGGL(lfull_listed_kernel, dim3(kListedBlocks), dim3(kLfThreads), 0, stream, a);
+        else if (tile_tokens == kLnBM)
+            hipLaunchKernelGGL(lfull_narrow_kernel, grid, dim3(kLnThreads), 0, stream, a);
         else
-            hipLaunchKernelGGL(lfull_tile_kernel, dim3((unsigned)(tiles * p.ntiles)), dim3(kLfThreads), 0, stream, a);
+            hipLaunchKernelGGL(lfull_tile_kernel, grid, dim3(kLfThreads), 0, stream, a);
         if (launch_status() != HSCALE_OK) return HSCALE_ERR_HIP;
         if (gram)
             hipLaunchKernelGGL(gram_fallback, dim3((unsigned)((out + 255) / 256)), dim3(256), 0, stream, partial, tiles,

@@ -46,29 +46,6 @@ constexpr int64_t kGrMaxUnits = 4608;  // partial tiles per pass (1.2 GB of work
 constexpr int64_t kGrMaxTiles = 64;    // in <= 16384
 constexpr uint32_t kGrOutside = 0x7FFF0000u;  // beyond every descriptor's range
 
-// Raw buffer descriptor of `bytes` bytes at a wave-uniform address.
-__device__ __forceinline__ u32x4 raw_descriptor(const void *p, uint32_t bytes) {
-    const uint64_t a = reinterpret_cast<uintptr_t>(p);
-    return u32x4{(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a),
-                 (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32) & 0xFFFF),
-                 (uint32_t)__builtin_amdgcn_readfirstlane((int)bytes), kRawBufferWord3};
-}
-
-// Starts a copy of 16 bytes per lane from the buffer to LDS at `dst` + 16 x
-// lane; the caller waits for vmcnt.  In assembly because the compiler, which
-// cannot tell the buffer being filled from the one being read, would put a
-// wait for the builtin's copies before every transposed read.  It writes no
-// register but M0, which nothing else in the kernel uses.
-__device__ __forceinline__ void load_to_lds(u32x4 rsrc, uint32_t offset, uint32_t dst) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                 :
-                 : "s"(dst), "v"(offset), "s"(rsrc)
-                 : "memory");
-}
-
-constexpr int kWaitAll = 0x70;  // s_waitcnt vmcnt(0) lgkmcnt(0)
-constexpr int kSchedMfma = 0x008, kSchedLdsRead = 0x100;  // instruction classes of the scheduling groups
-
 struct GramArgs {
     const u32x4 *X;  // [tokens, in] bf16, of this pass
     int64_t tokens, in;
@@ -470,11 +447,18 @@ __global__ __launch_bounds__(kGrThreads, 2) void gram_apply(const GramApplyArgs 
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
+                for (int j = 0; j < 2; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fg1[kk][i], fh[kk][j], acc[i][j], 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fg2[kk][i], fh[kk][j], acc[i][j], 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fg1[kk][i], fl[kk][j], acc[i][j], 0, 0, 0);
-                }
 #pragma unroll
             for (int i = 0; i < 12; ++i) {
                 __builtin_amdgcn_sched_group_barrier(kSchedMfma, 2, 0);

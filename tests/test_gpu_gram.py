@@ -147,3 +147,20 @@ def test_squares_outside_fp32_go_direct(hs, scale):
     gram, plain = _both(hs, X, W, s_g, codes, packed)
     assert torch.isfinite(gram).all()
     assert ((gram - plain).abs() <= 1e-12 * plain).all()
+
+
+# The direct route's two tiles: 128 tokens where those fill the CUs in fewer
+# rounds, 384 otherwise (the last case); edges of both, ragged rows and columns.
+@pytest.mark.parametrize("T,n,m", [(1, 16, 1), (127, 32, 255), (129, 48, 257), (385, 1040, 513), (2049, 528, 4100),
+                                   (4096, 256, 4096)])
+def test_direct_tiles_and_smaller_workspaces(hs, T, n, m):
+    X, W = _case(T, n, m, seed=T + m)
+    s_g, codes, packed = _stored(hs, W)
+    ref = _reference(X, W, s_g, codes, packed)
+    full = hs.output_error(X, W, s_g, codes, packed)
+    least = torch.empty(_direct_bytes(T, n, m), dtype=torch.uint8, device=DEV)
+    passes = hs.output_error(X, W, s_g, codes, packed, workspace=least)  # narrow tiles in up to three passes
+    torch.cuda.synchronize()
+    print(f"[direct {T}x{n}x{m}] max rel {_rel(full, ref):.2e}", flush=True)
+    assert _rel(full, ref) <= REL_TOL
+    assert ((full - passes).abs() <= 1e-12 * full).all()
