@@ -103,6 +103,8 @@ const char *hscale_status_string(int status);
  * activations: fp64 partial sums of each token slice, so that the cross-slice
  * reduction is a fixed-order tree (deterministic, no atomics).  Depends only
  * on (tokens, in).  Returns 0 when tokens == 0 or the sizes are invalid.
+ * hscale_hdiag also accepts a smaller workspace that holds the partials of
+ * slices of at least 256 tokens, and then takes those slices.
  */
 size_t hscale_hdiag_workspace_bytes(int64_t tokens, int64_t in);
 
@@ -364,7 +366,7 @@ size_t hscale_output_error_workspace_bytes(int64_t tokens, int64_t in,
  * calls add up; zero it first.
  *
  * Arithmetic: dW is formed in fp32 with one rounding.  The direct product
- * splits it into two bf16 parts hi + lo (within 2^-18 |dW|) and computes
+ * splits it into two bf16 parts hi + lo (within 2^-16 |dW|) and computes
  * X dW^T on the matrix cores as bf16 products accumulated in fp32; squares
  * and sums are fp64 in a fixed order.  Where many output rows share a long X
  * (a rule on the sizes) and the workspace holds what

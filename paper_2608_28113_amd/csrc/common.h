@@ -61,10 +61,11 @@ __global__ __launch_bounds__(kTreeThreads) void hdiag_tree(const double *__restr
     }
 }
 
-// Lanes per column for summing `slices` partials: about 16 or fewer slices
-// per lane, so the per-lane chains stay short and small column counts still
-// spread over many blocks.
-inline int tree_lanes(int64_t slices) { return slices <= 64 ? 4 : slices <= 256 ? 16 : 64; }
+// Lanes per column for summing `slices` partials: at most about 16 slices per
+// lane, so the per-lane chains stay short and small column counts still
+// spread over many blocks; about 4 for the 64 slices of a 2048-token sequence,
+// where the call is a few microseconds in all.
+inline int tree_lanes(int64_t slices) { return slices <= 16 ? 4 : slices <= 256 ? 16 : 64; }
 
 // Launches the fixed-order column sum of slices x in partials.
 template <bool kAccumulate>

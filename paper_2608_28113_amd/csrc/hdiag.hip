@@ -8,6 +8,7 @@
 //                  block's four waves combine through LDS in a fixed order
 //                  and one fp64 partial per (slice, column) goes to the
 //                  caller's workspace.
+//   hdiag_small    the whole sum of at most 4096 tokens in one launch.
 //   hdiag_tree     fixed-order fp64 sum of the slice partials, one fp32 h per
 //                  column (4, 16 or 64 lanes per column by slice count).  No atomics: results are bit-identical run to run.
 
@@ -29,12 +30,34 @@ constexpr int kHdLaneCols = 8;                 // bf16 per 16-byte load
 constexpr int kHdTileCols = 64 * kHdLaneCols;  // 512 columns per block
 constexpr int kHdChunk = 32;                   // fp32 chain length per lane
 constexpr int kHdUnroll = 8;                   // row loads in flight per lane
+constexpr int kHdTail = 4;                     // and of the rows left over
 // Grid size: as many blocks as MI355X keeps resident at once (256 CUs x 7
 // blocks of 4 waves at this kernel's 68 VGPRs), so the whole grid runs in
-// one round with no tail.  The plan depends only on (tokens, in), which
-// keeps results identical from run to run.
+// one round with no tail.  The plan depends only on (tokens, in) and on
+// whether the workspace holds it, which keeps results identical from run to
+// run.
 constexpr int kHdTargetBlocks = 1792;
-constexpr int64_t kHdMinSliceTokens = 256;
+// Up to this many tokens one launch does the whole sum (hdiag_small), and up
+// to the smaller number with 16 rows at once in blocks of 256 threads.
+constexpr int64_t kHdSmallTokens = 1024;
+constexpr int64_t kHdFewTokens = 256;
+// Slices of 256 tokens or more; where those give fewer than 192 blocks,
+// shorter ones (down to one batch of loads per lane) for 512 blocks: their
+// partials cost up to 25% of X's traffic, an idle CU more.  Measured, both
+// kernels: 2048 tokens x 4096 columns 11.4 us in 64 blocks, 8.6 in 512; x 512
+// columns 10.6 and 6.1; 4096 x 4096 14.4 and 12.4; but 2048 x 14336 14.3 in
+// 224 blocks and 15.4 in 448.
+constexpr int64_t kHdSliceTokens = 256;
+constexpr int64_t kHdBatchTokens = kHdWaves * kHdUnroll;
+constexpr int64_t kHdFewBlocks = 192, kHdEnoughBlocks = 512;
+// Blocks that start a multiple of 2 MB apart run through the same memory
+// channels together, as long as they stay in step (short slices): 32 tokens
+// more per slice then, and shorter slices up to 512 blocks.  Measured with
+// 4096 columns at 16384 tokens: 37.1 us, 25.5 with the 32 more; at 32768 62.1
+// and 47.1; with 8192 columns at 8192 tokens 33.8 and 26.2.  Slices 1, 2.5 or
+// 3.5 MB apart (2048, 5120 and 14336 columns) gain nothing, and lose 1-3%.
+constexpr int64_t kHdAlias = ((int64_t)2 << 20) / 2;  // in elements
+constexpr int64_t kHdLongSliceTokens = 1024;
 
 struct HdiagPlan {
     int64_t tiles = 0;
@@ -42,18 +65,30 @@ struct HdiagPlan {
     int64_t slice_tokens = 0;
 };
 
-HdiagPlan hdiag_plan(int64_t tokens, int64_t in) {
+HdiagPlan hdiag_plan(int64_t tokens, int64_t in, bool coarse) {
     HdiagPlan p;
     if (tokens <= 0 || in <= 0) return p;
     p.tiles = (in + kHdTileCols - 1) / kHdTileCols;
-    int64_t slices = kHdTargetBlocks / p.tiles;
-    int64_t max_slices = (tokens + kHdMinSliceTokens - 1) / kHdMinSliceTokens;
-    if (slices > max_slices) slices = max_slices;
+    const int64_t resident = kHdTargetBlocks / p.tiles;
+    int64_t slices = (tokens + kHdSliceTokens - 1) / kHdSliceTokens;
+    if (slices > resident) slices = resident;
+    const bool fine = !coarse && tokens > kHdSmallTokens;  // hdiag_small uses no partials
     if (slices < 1) slices = 1;
     p.slice_tokens = (tokens + slices - 1) / slices;
+    if (fine) {
+        auto aliased = [&] { return p.slice_tokens < kHdLongSliceTokens && p.slice_tokens * in % kHdAlias == 0; };
+        if (slices * p.tiles < (aliased() ? kHdEnoughBlocks : kHdFewBlocks)) {
+            slices = (kHdEnoughBlocks + p.tiles - 1) / p.tiles;
+            p.slice_tokens = (tokens + slices - 1) / slices;
+            p.slice_tokens = (p.slice_tokens + kHdBatchTokens - 1) / kHdBatchTokens * kHdBatchTokens;
+        }
+        if (aliased()) p.slice_tokens += kHdBatchTokens;
+    }
     p.slices = (tokens + p.slice_tokens - 1) / p.slice_tokens;
     return p;
 }
+
+size_t hdiag_bytes(const HdiagPlan &p, int64_t in) { return (size_t)p.slices * (size_t)in * sizeof(double); }
 
 __device__ __forceinline__ void hd_accumulate(float (&acc)[kHdLaneCols], const u32x4 &v) {
     const uint32_t d[4] = {v.x, v.y, v.z, v.w};
@@ -97,15 +132,15 @@ __global__ __launch_bounds__(kHdThreads) void hdiag_partial(const u32x4 *__restr
         const int64_t vec_per_row = in / kHdLaneCols;
         // This wave's rows: t0 + wave, t0 + wave + 4, ... < t1.
         const int64_t first = t0 + wave;
-        const int64_t rows = first < t1 ? (t1 - first + kHdWaves - 1) / kHdWaves : 0;
+        // (fewer than 2^30: a slice of the largest X accepted has 2^46 / 512 / 1792 tokens, or 2^42 / 1792)
+        const int rows = first < t1 ? (int)((t1 - first + kHdWaves - 1) / kHdWaves) : 0;
         const u32x4 *p = X + (rows > 0 ? first * vec_per_row + col / kHdLaneCols : 0);
         const int64_t stride = (int64_t)kHdWaves * vec_per_row;
-        int64_t r = 0;
-        int since_fold = 0;
-        for (; r + kHdUnroll <= rows; r += kHdUnroll) {
+        int r = 0, since_fold = 0;
+        for (; r + kHdUnroll <= rows; r += kHdUnroll, p += kHdUnroll * stride) {
             u32x4 v[kHdUnroll];
 #pragma unroll
-            for (int u = 0; u < kHdUnroll; ++u) v[u] = __builtin_nontemporal_load(p + (r + u) * stride);
+            for (int u = 0; u < kHdUnroll; ++u) v[u] = __builtin_nontemporal_load(p + u * stride);
 #pragma unroll
             for (int u = 0; u < kHdUnroll; ++u) hd_accumulate(acc, v[u]);
             since_fold += kHdUnroll;
@@ -114,9 +149,13 @@ __global__ __launch_bounds__(kHdThreads) void hdiag_partial(const u32x4 *__restr
                 since_fold = 0;
             }
         }
-        for (; r < rows; ++r) {
-            const u32x4 v = __builtin_nontemporal_load(p + r * stride);
-            hd_accumulate(acc, v);
+        for (; r < rows; r += kHdTail, p += kHdTail * stride) {  // at most 7 rows: the chain stays within 24 + 8
+            u32x4 v[kHdTail];
+#pragma unroll
+            for (int u = 0; u < kHdTail; ++u)
+                v[u] = r + u < rows ? __builtin_nontemporal_load(p + u * stride) : u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int u = 0; u < kHdTail; ++u) hd_accumulate(acc, v[u]);
         }
         hd_fold(acc, acc64);
     }
@@ -134,6 +173,73 @@ __global__ __launch_bounds__(kHdThreads) void hdiag_partial(const u32x4 *__restr
         s.y = ((red[0][c + 1] + red[1][c + 1]) + red[2][c + 1]) + red[3][c + 1];
         *reinterpret_cast<double2 *>(partial + slice * in + gcol) = s;
     }
+}
+
+// The whole sum of a short X in one launch: kRowLanes lanes to a row (8
+// columns each), kThreads / kRowLanes rows at once, up to 32 rows per lane in
+// fp32; then fp64 in a fixed order, across the wave's rows by shuffles and
+// across waves through LDS.  A block has its columns for itself, so there are
+// no partials, no second launch and no wait between the two.  A CU draws
+// about 130 GB/s, so few blocks suffice while tokens are few: 1024 threads
+// with 16 KB each of loads in flight per wave reach most of the memory rate
+// from one block per CU.
+// Measured: 128 x 512 3.5 us, in two launches 6.3; 512 x 4096 5.6 and 10.3;
+// 1024 x 4096 7.0 and 10.5; at 2048 tokens its two batches of loads one after
+// the other take 10.7 us against 8.6 in two launches of more blocks.
+template <bool kAccumulate, int kThreads, int kRowLanes>
+__global__ __launch_bounds__(kThreads) void hdiag_small(const u32x4 *__restrict__ X, int tokens, int64_t in,
+                                                        float *__restrict__ h, double *__restrict__ h64) {
+    constexpr int kCols = kRowLanes * kHdLaneCols, kRows = kThreads / kRowLanes, kWaves = kThreads / 64;
+    __shared__ double red[kWaves][kCols];
+    const int q = threadIdx.x / kRowLanes, lane = threadIdx.x % kRowLanes;
+    const int64_t col = (int64_t)blockIdx.x * kCols + lane * kHdLaneCols;
+    float acc[kHdLaneCols];
+#pragma unroll
+    for (int k = 0; k < kHdLaneCols; ++k) acc[k] = 0.0f;
+    if (col < in) {
+        const int64_t vec_per_row = in / kHdLaneCols;
+        const u32x4 *p = X + col / kHdLaneCols;
+        for (int r = q; r < tokens; r += kRows * kHdUnroll) {
+            u32x4 v[kHdUnroll];
+#pragma unroll
+            for (int u = 0; u < kHdUnroll; ++u) {
+                const int t = r + u * kRows;
+                v[u] = t < tokens ? __builtin_nontemporal_load(p + (int64_t)t * vec_per_row) : u32x4{0u, 0u, 0u, 0u};
+            }
+#pragma unroll
+            for (int u = 0; u < kHdUnroll; ++u) hd_accumulate(acc, v[u]);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < kHdLaneCols; ++k) {
+        double s = (double)acc[k];
+#pragma unroll
+        for (int o = kRowLanes; o < 64; o <<= 1) s += __shfl_xor(s, o, 64);
+        if ((threadIdx.x & 63) < kRowLanes) red[threadIdx.x >> 6][lane * kHdLaneCols + k] = s;
+    }
+    __syncthreads();
+    const int64_t c = (int64_t)blockIdx.x * kCols + threadIdx.x;
+    if (threadIdx.x < kCols && c < in) {
+        double s = red[0][threadIdx.x];
+#pragma unroll
+        for (int k = 1; k < kWaves; ++k) s += red[k][threadIdx.x];
+        if (kAccumulate)
+            h64[c] += s;
+        else
+            h[c] = (float)s;
+    }
+}
+
+template <int kThreads, int kRowLanes>
+void launch_small(const void *X, int64_t tokens, int64_t in, float *h, double *h64, hipStream_t stream) {
+    constexpr int kCols = kRowLanes * kHdLaneCols;
+    const dim3 blocks((unsigned)((in + kCols - 1) / kCols));
+    if (h64)
+        hipLaunchKernelGGL((hdiag_small<true, kThreads, kRowLanes>), blocks, dim3(kThreads), 0, stream,
+                           static_cast<const u32x4 *>(X), (int)tokens, in, nullptr, h64);
+    else
+        hipLaunchKernelGGL((hdiag_small<false, kThreads, kRowLanes>), blocks, dim3(kThreads), 0, stream,
+                           static_cast<const u32x4 *>(X), (int)tokens, in, h, nullptr);
 }
 
 __global__ __launch_bounds__(256) void hdiag_finalize_kernel(const double *__restrict__ h64, int64_t in,
@@ -168,8 +274,9 @@ int hdiag_run(const void *X, int64_t tokens, int64_t in, float *h, double *h64, 
     const int status = hdiag_check_io(X, tokens, in, h, h64);
     if (status != HSCALE_OK || in == 0) return status;
     const bool accumulate = h64 != nullptr;
-    const HdiagPlan p = hdiag_plan(tokens, in);
-    const size_t need = hscale_hdiag_workspace_bytes(tokens, in);
+    HdiagPlan p = hdiag_plan(tokens, in, false);
+    if (workspace_bytes < hdiag_bytes(p, in)) p = hdiag_plan(tokens, in, true);
+    const size_t need = hdiag_bytes(p, in);
     const size_t nout = accumulate ? (size_t)in * 8 : (size_t)in * 4;
     const void *out = accumulate ? (const void *)h64 : (const void *)h;
     if (tokens > 0) {
@@ -178,6 +285,13 @@ int hdiag_run(const void *X, int64_t tokens, int64_t in, float *h, double *h64, 
         if (!aligned(workspace, 16)) return HSCALE_ERR_ALIGN;
         const size_t nx = (size_t)tokens * (size_t)in * 2;
         if (overlaps(workspace, need, X, nx) || overlaps(workspace, need, out, nout)) return HSCALE_ERR_OVERLAP;
+        if (tokens <= kHdSmallTokens) {
+            if (tokens <= kHdFewTokens)
+                launch_small<256, 16>(X, tokens, in, h, h64, stream);
+            else
+                launch_small<1024, 8>(X, tokens, in, h, h64, stream);
+            return launch_status();
+        }
         dim3 grid((unsigned)p.tiles, (unsigned)p.slices);
         hipLaunchKernelGGL(hdiag_partial, grid, dim3(kHdThreads), 0, stream, static_cast<const u32x4 *>(X),
                            tokens, in, p.slice_tokens, static_cast<double *>(workspace));
@@ -253,8 +367,7 @@ const char *hscale_status_string(int status) {
 
 size_t hscale_hdiag_workspace_bytes(int64_t tokens, int64_t in) {
     if (tokens <= 0 || in <= 0 || in % kGroup != 0) return 0;
-    const HdiagPlan p = hdiag_plan(tokens, in);
-    return (size_t)p.slices * (size_t)in * sizeof(double);
+    return hdiag_bytes(hdiag_plan(tokens, in, false), in);
 }
 
 int hscale_hdiag(const void *X, int64_t tokens, int64_t in, float *h, void *workspace, size_t workspace_bytes,

@@ -1,0 +1,43 @@
+"""hdiag at the edges of its plans: one launch for few tokens (16 rows at once
+up to 256 tokens, 128 rows up to 1024), short slices, slices moved off a
+2 MB spacing, and the coarse slices of a smaller workspace."""
+from __future__ import annotations
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def hs():
+    import paper_2608_28113_amd as hs
+    assert torch.cuda.is_available()
+    return hs
+
+
+@pytest.mark.parametrize("T,n", [(1, 16), (15, 112), (128, 512), (256, 144), (257, 64), (1024, 1040), (1025, 1040),
+                                 (1056, 4096), (2040, 4096), (4095, 528), (2048, 14336), (8192, 4096), (8193, 8192),
+                                 (65537, 48)])
+def test_hdiag_plans(hs, T, n):
+    g = torch.Generator(device=DEV).manual_seed(T * 31 + n)
+    X = (torch.randn((T, n), generator=g, device=DEV) * torch.exp(torch.randn(n, generator=g, device=DEV))).bfloat16()
+    ref = X.double().square_().sum(0)
+    h = hs.hdiag(X)
+    # Slices of at least 256 tokens: what a workspace of that size is given.
+    slices = max(1, min(1792 // -(-n // 512), -(-T // 256)))
+    coarse = -(-T // -(-T // slices)) * n * 8
+    assert coarse <= hs.hdiag_workspace_bytes(T, n)
+    h_coarse = hs.hdiag(X, workspace=torch.empty(coarse, dtype=torch.uint8, device=DEV))
+    h64 = torch.zeros(n, dtype=torch.float64, device=DEV)
+    hs.hdiag_accumulate(X, h64)
+    h_acc = hs.hdiag_finalize(h64)
+    torch.cuda.synchronize()
+    for name, v in (("hdiag", h), ("coarse", h_coarse), ("accumulated", h_acc)):
+        rel = ((v.double() - ref).abs() / ref.clamp_min(1e-30)).max().item()
+        print(f"[{T}x{n}] {name} max rel {rel:.2e}", flush=True)
+        assert rel <= 2e-6  # chains of at most 32 fp32 additions: 31.5 x 2^-24
+    assert torch.equal(h, h_acc)
+    assert torch.equal(h, hs.hdiag(X))
