@@ -410,6 +410,100 @@ __global__ __launch_bounds__(kSearchThreads) void search_kernel(const SearchArgs
     }
 }
 
+// A search of few groups: four lanes share a group, each taking every fourth
+// shift, so that a launch too small for one group per lane still reaches all
+// SIMDs and walks a quarter of the window in each wave.  The per-group work
+// (loads, initial code) is done by all four, and W and h are loaded before the
+// scale table is built, since nothing else hides either latency.  Scores and
+// nibbles are those of the other walks; the lanes' minima combine to the
+// first minimum in increasing d, and the lane that holds it writes.
+constexpr int kSplit = 4;
+// Whether a search is small enough for that.  Measured against one group per
+// lane: 32768 groups take 5.4 against 4.6 us at 9 candidates, 7.1 against 4.6
+// at 16, 18.7 against 9.3 at 65 (about 4.5 us is the launch itself); 65536
+// groups 5.3 against 5.8 at 9, 8.2 against 5.9 at 16; 131072 groups 6.0
+// against 8.2 at 9, 9.0 against 8.2 at 16, 10.6 against 10.1 at 24.
+inline bool split_pays(int64_t groups, int candidates) {
+    return groups <= 32768 ? candidates >= 8 : groups <= 65536 && candidates >= 16;
+}
+
+template <int kInit, bool kStats>
+__global__ __launch_bounds__(kSearchThreads) void search_split_kernel(const SearchArgs a) {
+    __shared__ ScaleEntry tab[kTabSize];
+    __shared__ ScaleEntry uniq[kMaxCode + 1];
+    const int sub = threadIdx.x % kSplit;
+    const uint32_t g = blockIdx.x * (kSearchThreads / kSplit) + threadIdx.x / kSplit;
+    const bool live = g < a.num_groups;
+    const uint32_t gl = live ? g : 0, r = gl / a.Gc, i = gl % a.Gc;
+    const u32x4 *src = a.W + (uint64_t)r * a.ldw_vec + 2 * (uint64_t)i;
+    const u32x4 w0 = src[0], w1 = src[1];
+    const float4 *hsrc = a.h + 4 * (uint64_t)i;
+    float hh[kGroup];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const float4 v = hsrc[q];
+        hh[4 * q] = v.x;
+        hh[4 * q + 1] = v.y;
+        hh[4 * q + 2] = v.z;
+        hh[4 * q + 3] = v.w;
+    }
+    const int given = kInit == kInitGiven ? (int)a.init[(uint64_t)r * a.ldi + i] : 0;
+    build_scale_table(tab, uniq, a.s_g);
+    if (!live) return;  // whole quads: the exchange below stays within live lanes
+
+    float w[kGroup];
+    unpack_group(w0, w1, w);
+    const int c0 = initial_code<kInit>(w, tab, a.s_g, given);
+    const ScaleEntry *col = tab + (c0 + kTabPad);
+    float best_e = INFINITY, e_init = 0.0f;
+    int best_d = INT_MAX;
+    uint2 best_p = make_uint2(0u, 0u), pa = best_p, pb = best_p;
+    for (int d = -a.down + sub; d <= a.up; d += 2 * kSplit) {
+        // Two candidates at a time; a second one past the window is scored
+        // (its table entry exists: up <= 125) but not kept.
+        const int d1 = min(d + kSplit, kMaxWindow);
+        const ScaleEntry sa = col[d], sb = col[d1];
+        pa = quantize_group(w, sa.R, pa);
+        pb = quantize_group(w, sb.R, pb);
+        const float ea = group_error(w, hh, pa, sa.S);
+        const float eb = group_error(w, hh, pb, sb.S);
+        if (kStats) {
+            if (d == 0) e_init = ea;
+            if (d + kSplit == 0) e_init = eb;
+        }
+        if (ea < best_e || (ea == best_e && d < best_d)) {
+            best_e = ea;
+            best_d = d;
+            best_p = pa;
+        }
+        if (d + kSplit <= a.up && eb < best_e) {
+            best_e = eb;
+            best_d = d1;
+            best_p = pb;
+        }
+    }
+    float e_min = best_e;
+    int d_min = best_d;
+#pragma unroll
+    for (int o = 1; o < kSplit; o <<= 1) {
+        const float eo = __shfl_xor(e_min, o, 64);
+        const int d_o = __shfl_xor(d_min, o, 64);
+        if (eo < e_min || (eo == e_min && d_o < d_min)) {
+            e_min = eo;
+            d_min = d_o;
+        }
+        if (kStats) e_init += __shfl_xor(e_init, o, 64);  // one lane holds it, the others 0
+    }
+    if (best_d != d_min) return;
+    a.codes[(uint64_t)r * a.ldc + i] = (uint8_t)min(max(c0 + d_min, 1), kMaxCode);
+    a.packed[(uint64_t)r * a.ldp_vec + i] = best_p;
+    if (kStats) {
+        a.shift[g] = (int8_t)d_min;
+        a.err_best[g] = e_min;
+        a.err_init[g] = e_init;
+    }
+}
+
 // Several independent layers searched by one launch, with the same shift
 // set and initial-code rule.  The layers' arrays are contiguous.  Each block
 // covers 256 consecutive groups of one layer and finds that layer among the
@@ -508,6 +602,18 @@ __global__ __launch_bounds__(kSearchThreads) void quantize_kernel(const u32x4 *_
         load_group(W, g, w);
         const int c = min(max((int)codes[g], 1), kMaxCode);
         packed[g] = quantize_group(w, tab[c + kTabPad].R, make_uint2(0u, 0u));
+    }
+}
+
+template <bool kStats>
+void launch_split(int init_mode, dim3 grid, hipStream_t stream, const SearchArgs &a) {
+    const dim3 block(kSearchThreads);
+    switch (init_mode) {
+        case kInitMaxAbs: hipLaunchKernelGGL((search_split_kernel<kInitMaxAbs, kStats>), grid, block, 0, stream, a); break;
+        case kInitFourOverSix:
+            hipLaunchKernelGGL((search_split_kernel<kInitFourOverSix, kStats>), grid, block, 0, stream, a);
+            break;
+        default: hipLaunchKernelGGL((search_split_kernel<kInitGiven, kStats>), grid, block, 0, stream, a); break;
     }
 }
 
@@ -623,7 +729,13 @@ int search_block(const void *W, int64_t ldw, int64_t out, int64_t cols, const fl
     const bool flat = ldw == cols && ldc == Gc && ldp == cols / 2 && (init_mode != kInitGiven || ldi == Gc) &&
                       groups <= ((int64_t)1 << 27) && cols <= ((int64_t)1 << 28);
     const dim3 grid(grid_for(groups, kSearchThreads)), block(kSearchThreads);
-    if (flat)
+    if (split_pays(groups, down + up + 1)) {
+        const dim3 quads((unsigned)((groups * kSplit + kSearchThreads - 1) / kSearchThreads));
+        if (stats)
+            launch_split<true>(init_mode, quads, stream, a);
+        else
+            launch_split<false>(init_mode, quads, stream, a);
+    } else if (flat)
         launch_search<true>(init_mode, stats, grid, block, stream, a);
     else
         launch_search<false>(init_mode, stats, grid, block, stream, a);
