@@ -298,3 +298,28 @@ def test_shift_summary_exact_groups_on_gpu(hs):
     rel = want.astype(np.float64)
     rel[down] = 0.0
     assert np.array_equal(s["sum_rel"], rel)
+
+
+# Bins on both sides of the line (20) up to which each thread keeps sums of its
+# own; group counts around a block's 4096; shifts outside the window dropped.
+@pytest.mark.parametrize("down,up", [(0, 0), (4, 4), (9, 10), (10, 10), (125, 125)])
+@pytest.mark.parametrize("groups", [1, 4095, 4097, 20011])
+def test_shift_summary_bins(hs, down, up, groups):
+    rng = np.random.default_rng(groups + down)
+    shift = rng.integers(max(-128, -down - 1), min(127, up + 1) + 1, groups).astype(np.int8)
+    ei = np.exp(rng.standard_normal(groups)).astype(np.float32)
+    ei[::7] = 0.0
+    eb = (ei * rng.random(groups)).astype(np.float32)
+    t = [torch.from_numpy(v).to(DEV) for v in (shift, eb, ei)]
+    s, again = _np(hs.shift_summary(*t, down, up)), _np(hs.shift_summary(*t, down, up))
+    d = shift.astype(np.int64) + down
+    keep = (d >= 0) & (d <= down + up)
+    a, b = ei.astype(np.float64), eb.astype(np.float64)
+    rel = np.where(a > 0, (a - b) / np.where(a > 0, a, 1.0), 0.0)
+    K = down + up + 1
+    assert np.array_equal(s["count"], np.bincount(d[keep], minlength=K))
+    for key, v in (("sum_init", a), ("sum_best", b), ("sum_rel", rel)):
+        want = np.bincount(d[keep], weights=v[keep], minlength=K)
+        # fp64 sums of at most 20011 non-negative terms in another order
+        assert np.all(np.abs(s[key] - want) <= 20011 * 2.0 ** -53 * want), key
+    assert all(np.array_equal(s[k], again[k]) for k in s)
