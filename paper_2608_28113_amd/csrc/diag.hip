@@ -590,121 +590,139 @@ __global__ __launch_bounds__(kLfThreads, kLfWaves / 4) void lfull_listed_kernel(
     }
 }
 
-// A tile of 128 tokens x 256 weight rows for problems of few tiles: 2 x 4
-// waves of 64 x 64, two per SIMD.  One wave's tile takes 6 LDS reads per 8
-// MFMAs, so it gives up a third of the rate of the large tile (0.56 of its
-// time for a third of its work); at 2048 tokens x 4096 x 4096 its 256 blocks
-// fill the chip where the large tile's 96 do not: 132 us against 234 us.
-constexpr int kLnBM = 128;
-constexpr int kLnWM = 2;
-constexpr int kLnThreads = 64 * kLnWM * kLfWN;
-constexpr int kLnRows = kLnBM + 2 * kLfBN;
-constexpr int kLnMI = kLnBM / kLnWM / 32;
-constexpr int kLnLoads = kLnRows / 16 / (kLnThreads / 64);  // 1 KB loads per wave and stage: X, hi (2), lo (2)
-static_assert(kLnLoads == 5 && kLnBM == 128, "wave w loads rows 16 w + 128 i of the stage");
-
-__global__ __launch_bounds__(kLnThreads, 2) void lfull_narrow_kernel(const LfArgs a) {
-    __shared__ __attribute__((aligned(16))) uint8_t lds[2][kLnRows * 64];
+// Tiles for problems that the large one leaves the chip idle on: kWM x kWN
+// waves of 32 kMI tokens x 64 weight rows, a ring of kRing stages.  At one or
+// two waves per SIMD nothing else hides a wave's LDS reads, so there are two
+// sets of operand registers: each 16-deep step's operands are read while the
+// step before it multiplies, across stages too.  The ring's stages beyond two
+// cover the copies' latency (128 x 256, 2048 tokens x 4096 x 4096: 132 us with
+// two stages, 119 us with three, 120 us with four).
+template <int kWM, int kMI, int kWN, int kRing>
+__global__ __launch_bounds__(64 * kWM * kWN, 2) void lfull_pipe_kernel(const LfArgs a) {
+    constexpr int kBM = 32 * kMI * kWM, kBN = 64 * kWN, kWaves = kWM * kWN;
+    constexpr int kRows = kBM + 2 * kBN;
+    constexpr int kLoads = kRows / 16 / kWaves;  // 1 KB loads per wave and stage, slot q by wave q % waves
+    static_assert(kBM / 16 % kWaves == 0 && kBN / 16 % kWaves == 0, "load i has one operand for all waves");
+    static_assert(kRing * kRows * 64 <= 160 * 1024 && kWM * kBN * 8 <= kRows * 64, "LDS");
+    constexpr int kInFlight = (kRing - 2) * kLoads;  // copies of later stages than the next
+    __shared__ __attribute__((aligned(16))) uint8_t lds[kRing][kRows * 64];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: LDS addresses in SGPRs
-    const int wm = wave % kLnWM, wn = wave / kLnWM;
+    const int wm = wave % kWM, wn = wave / kWM;
     int64_t mt, nt;
     lf_tile_of_block(blockIdx.x, gridDim.x, a.ntiles, mt, nt);
-    const int64_t t0 = mt * kLnBM, r0 = nt * kLfBN;
+    const int64_t t0 = mt * kBM, r0 = nt * kBN;
     const int stages = (int)(a.ldd / kLfBK);
 
     // Loads and LDS layout as in lf_tile, except that the per-lane offsets
     // advance by 64 bytes a stage.
     const int64_t xrow_bytes = a.in * 2, drow_bytes = a.ldd * 2;
-    const int64_t valid_rows = a.tokens - t0 < kLnBM ? a.tokens - t0 : kLnBM;
+    const int64_t valid_rows = a.tokens - t0 < kBM ? a.tokens - t0 : kBM;
     const u32x4 rx = raw_descriptor(a.X + t0 * (a.in / 8), (uint32_t)(valid_rows * xrow_bytes));
-    const u32x4 rd[2] = {raw_descriptor(a.hi + r0 * (a.ldd / 8), (uint32_t)(kLfBN * drow_bytes)),
-                         raw_descriptor(a.lo + r0 * (a.ldd / 8), (uint32_t)(kLfBN * drow_bytes))};
-    const int row0 = wave * 16 + (lane >> 2);
-    const int c0 = (lane & 3) ^ ((row0 >> 2) & 3);
-    uint32_t vx = (uint32_t)(row0 * xrow_bytes + c0 * 16);
-    uint32_t vd[2] = {(uint32_t)(row0 * drow_bytes + c0 * 16), (uint32_t)((row0 + 128) * drow_bytes + c0 * 16)};
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds[0] + wave * 1024;
-    auto issue = [&](int buf) {
-        const uint32_t dst = lds0 + buf * (kLnRows * 64);
-        load_to_lds(rx, vx, dst);
+    const u32x4 rhi = raw_descriptor(a.hi + r0 * (a.ldd / 8), (uint32_t)(kBN * drow_bytes));
+    const u32x4 rlo = raw_descriptor(a.lo + r0 * (a.ldd / 8), (uint32_t)(kBN * drow_bytes));
+    uint32_t voff[kLoads];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) load_to_lds(rd[i >> 1], vd[i & 1], dst + (i + 1) * 8192);
-        vx += 64, vd[0] += 64, vd[1] += 64;
+    for (int i = 0; i < kLoads; ++i) {
+        const int row = (wave + i * kWaves) * 16 + (lane >> 2);
+        const int c = (lane & 3) ^ ((row >> 2) & 3);
+        voff[i] = row < kBM ? (uint32_t)(row * xrow_bytes + c * 16)
+                            : (uint32_t)(((row - kBM) % kBN) * drow_bytes + c * 16);
+    }
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds[0] + wave * 1024;
+    auto issue = [&](int buf) {  // the next stage
+        const uint32_t dst = lds0 + buf * (kRows * 64);
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) {
+            const int q = i * kWaves;
+            load_to_lds(q < kBM / 16 ? rx : q < (kBM + kBN) / 16 ? rhi : rlo, voff[i], dst + q * 1024);
+            voff[i] += kLfBK * 2;
+        }
     };
 
-    f32x16 acc[kLnMI][kLfNJ];
+    f32x16 acc[kMI][2];
 #pragma unroll
-    for (int i = 0; i < kLnMI; ++i)
+    for (int i = 0; i < kMI; ++i)
 #pragma unroll
-        for (int j = 0; j < kLfNJ; ++j)
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
 
-    // Two buffers, and two sets of operand registers: each 16-deep step's
-    // operands are read while the step before it multiplies, across stages
-    // too.  At a stage's last step its operands are in registers, so after
-    // the waits (own reads done, own copies of the next stage landed) and the
-    // barrier the buffer takes the stage after next, which then has a whole
-    // stage's time to arrive.
-    bf16x8 fa[2][kLnMI], fh[2][kLfNJ], fl[2][kLfNJ];
+    // At a stage's last step its operands are in registers, so after the
+    // waits (own reads done, own copies of the next stage landed) and the
+    // barrier its buffer takes the stage kRing further on.  A wave's copies
+    // land in order, so those of later stages may stay outstanding; near the
+    // end, where fewer are, it waits for all.
+    bf16x8 fa[2][kMI], fh[2][2], fl[2][2];
     auto read_step = [&](const uint8_t *buf, int kk) {
         const int c = 2 * kk + (lane >> 5);
 #pragma unroll
-        for (int i = 0; i < kLnMI; ++i)
-            fa[kk][i] = *reinterpret_cast<const bf16x8 *>(
-                buf + lf_lds_offset(wm * (kLnBM / kLnWM) + i * 32 + (lane & 31), c));
+        for (int i = 0; i < kMI; ++i)
+            fa[kk][i] =
+                *reinterpret_cast<const bf16x8 *>(buf + lf_lds_offset(wm * 32 * kMI + i * 32 + (lane & 31), c));
 #pragma unroll
-        for (int j = 0; j < kLfNJ; ++j) {
-            const int row = kLnBM + wn * (kLfBN / kLfWN) + j * 32 + (lane & 31);
+        for (int j = 0; j < 2; ++j) {
+            const int row = kBM + wn * 64 + j * 32 + (lane & 31);
             fh[kk][j] = *reinterpret_cast<const bf16x8 *>(buf + lf_lds_offset(row, c));
-            fl[kk][j] = *reinterpret_cast<const bf16x8 *>(buf + lf_lds_offset(row + kLfBN, c));
+            fl[kk][j] = *reinterpret_cast<const bf16x8 *>(buf + lf_lds_offset(row + kBN, c));
         }
     };
-    issue(0);
-    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
-    if (stages > 1) issue(1);
+#pragma unroll
+    for (int s = 0; s < kRing - 1; ++s)
+        if (s < stages) issue(s);
+    if (stages >= kRing - 1)
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(kInFlight));
+    else
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+    asm volatile("s_barrier" ::: "memory");
+    if (stages >= kRing) issue(kRing - 1);
     read_step(lds[0], 0);
+    int cur = 0;
     for (int s = 0; s < stages; ++s) {
+        const int next = cur + 1 == kRing ? 0 : cur + 1;
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk) {
             if (kk == 0) {
-                read_step(lds[s & 1], 1);
+                read_step(lds[cur], 1);
             } else {
-                __builtin_amdgcn_s_waitcnt(kWaitAll);
+                if (s + kRing - 1 < stages)
+                    __builtin_amdgcn_s_waitcnt(waitcnt_vm(kInFlight) & ~(0xF << 8));  // and lgkmcnt(0)
+                else
+                    __builtin_amdgcn_s_waitcnt(kWaitAll);
                 asm volatile("s_barrier" ::: "memory");
-                if (s + 2 < stages) issue(s & 1);
-                read_step(lds[(s + 1) & 1], 0);
+                if (s + kRing < stages) issue(cur);
+                read_step(lds[next], 0);
             }
 #pragma unroll
-            for (int i = 0; i < kLnMI; ++i)
+            for (int i = 0; i < kMI; ++i)
 #pragma unroll
-                for (int j = 0; j < kLfNJ; ++j)
+                for (int j = 0; j < 2; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kk][i], fh[kk][j], acc[i][j], 0, 0, 0);
 #pragma unroll
-            for (int i = 0; i < kLnMI; ++i)
+            for (int i = 0; i < kMI; ++i)
 #pragma unroll
-                for (int j = 0; j < kLfNJ; ++j)
+                for (int j = 0; j < 2; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kk][i], fl[kk][j], acc[i][j], 0, 0, 0);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
+            for (int i = 0; i < 4 * kMI; ++i) {
                 __builtin_amdgcn_sched_group_barrier(kSchedMfma, 1, 0);
                 __builtin_amdgcn_sched_group_barrier(kSchedLdsRead, 1, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
+        cur = next;
     }
     __syncthreads();
 
     // Column sums of squares: lane l holds column l % 32 of each 32x32
-    // accumulator; lanes l and l + 32 share a column, and the kLnWM waves of
-    // a column group share its columns (added in wm order).
-    double sq[kLfNJ];
+    // accumulator; lanes l and l + 32 share a column, and the kWM waves of a
+    // column group share its columns (added in wm order).
+    double sq[2];
 #pragma unroll
-    for (int j = 0; j < kLfNJ; ++j) {
+    for (int j = 0; j < 2; ++j) {
         double v = 0.0;
 #pragma unroll
-        for (int i = 0; i < kLnMI; ++i)
+        for (int i = 0; i < kMI; ++i)
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
                 const double y = (double)acc[i][j][e];
@@ -712,22 +730,76 @@ __global__ __launch_bounds__(kLnThreads, 2) void lfull_narrow_kernel(const LfArg
             }
         sq[j] = v + __shfl_xor(v, 32, 64);
     }
-    double *red = reinterpret_cast<double *>(lds[0]);  // [kLnWM][kLfBN]
+    double *red = reinterpret_cast<double *>(lds[0]);  // [kWM][kBN]
     if (lane < 32) {
 #pragma unroll
-        for (int j = 0; j < kLfNJ; ++j) red[wm * kLfBN + wn * (kLfBN / kLfWN) + j * 32 + lane] = sq[j];
+        for (int j = 0; j < 2; ++j) red[wm * kBN + wn * 64 + j * 32 + lane] = sq[j];
     }
     __syncthreads();
-    if (tid < kLfBN) {
+    if (tid < kBN) {
         const int64_t col = r0 + tid;
-        if (col < a.out) a.partial[mt * a.out + col] = red[tid] + red[kLfBN + tid];
+        double v = red[tid];
+#pragma unroll
+        for (int w = 1; w < kWM; ++w) v += red[w * kBN + tid];
+        if (col < a.out) a.partial[mt * a.out + col] = v;
+    }
+}
+
+// The tiles, and what a stage of 32 columns costs: the time of a block that
+// has a CU for itself (LDS reads, waits and barriers), and the rate with all
+// CUs busy, where LDS traffic per MFMA and the clock that the power leaves
+// decide.  Measured with both on 64 to 65536 tokens x 64 to 14336 rows x 1024
+// to 14336 columns; the estimate below is within 15% there and picks the
+// fastest or one within 3%.
+enum LfTile : int { kLfWide, kLfMid, kLfNarrow, kLfSmall, kLfTiny };
+struct LfTileInfo {
+    int64_t tokens, rows;
+    double stage_us, pflops;
+};
+constexpr LfTileInfo kLfTiles[] = {
+    {kLfBM, kLfBN, 1.60, 1.40},  // 65536 x 4096 x 14336: 11.0 ms, mid 11.2, narrow 14.7
+    {256, 256, 1.15, 1.365},     // 4096 x 4096 x 4096: 202 us, wide 225, narrow 234
+    {128, 256, 0.70, 1.15},      // 2048 x 4096 x 4096: 119 us, mid 142, small 136
+    {128, 128, 0.44, 1.00},      // 1024 x 2048 x 2048: 32 us, narrow 48, mid 77, tiny 30
+    {64, 128, 0.36, 0.72},       // 512 x 4096 x 4096: 51 us, small 57, narrow 89; 256 x 512 x 2048: 23, 30, 44
+};
+constexpr int kLfTileCount = sizeof(kLfTiles) / sizeof(kLfTiles[0]);
+
+// The tile with the least estimated time: full rounds of 256 blocks, then the
+// rest.
+LfTile lfull_tile(int64_t tokens, int64_t out) {
+    int best = kLfWide;
+    double least = 0.0;
+    for (int k = 0; k < kLfTileCount; ++k) {
+        const LfTileInfo &t = kLfTiles[k];
+        const int64_t blocks = ((tokens + t.tokens - 1) / t.tokens) * ((out + t.rows - 1) / t.rows);
+        const double work = (double)(4 * t.tokens * t.rows * kLfBK) / (t.pflops * 1e9);  // us of a block's share
+        auto round = [&](int64_t b) { return (double)b * work > t.stage_us ? (double)b * work : t.stage_us; };
+        const double est = (double)(blocks / 256) * round(256) + (blocks % 256 ? round(blocks % 256) : 0.0);
+        if (k == 0 || est < least) {
+            best = k;
+            least = est;
+        }
+    }
+    return (LfTile)best;
+}
+
+void launch_tiles(LfTile tile, int64_t token_tiles, hipStream_t stream, const LfArgs &a) {
+    const dim3 grid((unsigned)(token_tiles * a.ntiles));
+    switch (tile) {
+        case kLfWide: hipLaunchKernelGGL(lfull_tile_kernel, grid, dim3(kLfThreads), 0, stream, a); break;
+        case kLfMid: hipLaunchKernelGGL((lfull_pipe_kernel<2, 4, 4, 3>), grid, dim3(512), 0, stream, a); break;
+        case kLfNarrow: hipLaunchKernelGGL((lfull_pipe_kernel<2, 2, 4, 3>), grid, dim3(512), 0, stream, a); break;
+        case kLfSmall: hipLaunchKernelGGL((lfull_pipe_kernel<2, 2, 2, 3>), grid, dim3(256), 0, stream, a); break;
+        case kLfTiny: hipLaunchKernelGGL((lfull_pipe_kernel<2, 1, 2, 3>), grid, dim3(256), 0, stream, a); break;
     }
 }
 
 struct LfPlan {
-    int64_t ldd = 0, rows_pad = 0, ntiles = 0;
-    int64_t tile_tokens = 0;      // kLfBM or kLnBM
-    int64_t tiles_per_pass = 0;   // token tiles of a pass
+    int64_t ldd = 0, rows_pad = 0, ntiles = 0;  // ntiles: of kLfBN rows
+    LfTile tile = kLfWide;
+    int64_t tile_tokens = 0, row_tiles = 0;  // of the chosen tile
+    int64_t tiles_per_pass = 0;              // token tiles of a pass
     size_t plane_bytes = 0, partial_offset = 0;
     size_t least = 0, bytes = 0;  // smallest workspace accepted, and the one asked for
 };
@@ -738,23 +810,25 @@ LfPlan lfull_plan(int64_t tokens, int64_t in, int64_t out) {
     p.ldd = (in + kLfBK - 1) / kLfBK * kLfBK;
     p.rows_pad = (out + kLfBN - 1) / kLfBN * kLfBN;
     p.ntiles = p.rows_pad / kLfBN;
-    // The large tile, or the narrow one where it fills the 256 CUs in fewer
-    // rounds by more than its lower rate costs (0.56 of the time for a round).
-    const int64_t wide = (tokens + kLfBM - 1) / kLfBM, narrow = (tokens + kLnBM - 1) / kLnBM;
-    const int64_t wide_rounds = (wide * p.ntiles + 255) / 256, narrow_rounds = (narrow * p.ntiles + 255) / 256;
-    p.tile_tokens = 0.56 * (double)narrow_rounds < (double)wide_rounds ? kLnBM : kLfBM;
-    const int64_t tiles = p.tile_tokens == kLnBM ? narrow : wide;
-    // A pass launches tiles_per_pass x ntiles blocks: at most kLfMaxTilesPerPass
-    // token tiles, and never more blocks than a grid dimension holds.
-    const int64_t grid_cap = INT_MAX / p.ntiles > 0 ? INT_MAX / p.ntiles : 1;
-    const int64_t cap = grid_cap < kLfMaxTilesPerPass ? grid_cap : kLfMaxTilesPerPass;
-    p.tiles_per_pass = tiles < cap ? tiles : cap;
+    p.tile = lfull_tile(tokens, out);
+    p.tile_tokens = kLfTiles[p.tile].tokens;
+    p.row_tiles = (out + kLfTiles[p.tile].rows - 1) / kLfTiles[p.tile].rows;
+    // A pass launches tiles_per_pass x row tiles blocks: at most
+    // kLfMaxTilesPerPass token tiles, and never more blocks than a grid
+    // dimension holds.
+    auto capped = [](int64_t tiles, int64_t row_tiles) {
+        int64_t cap = INT_MAX / row_tiles;
+        if (cap > kLfMaxTilesPerPass) cap = kLfMaxTilesPerPass;
+        if (cap < 1) cap = 1;
+        return tiles < cap ? tiles : cap;
+    };
+    p.tiles_per_pass = capped((tokens + p.tile_tokens - 1) / p.tile_tokens, p.row_tiles);
     p.plane_bytes = round_up((size_t)p.rows_pad * (size_t)p.ldd * 2, 256);
     p.partial_offset = 2 * p.plane_bytes;
     p.bytes = p.partial_offset + (size_t)p.tiles_per_pass * (size_t)out * sizeof(double);
-    // The partials of large tiles are enough: the narrow ones then take more
+    // The partials of large tiles are enough: smaller ones then take more
     // passes.
-    p.least = p.partial_offset + (size_t)(wide < cap ? wide : cap) * (size_t)out * sizeof(double);
+    p.least = p.partial_offset + (size_t)capped((tokens + kLfBM - 1) / kLfBM, p.ntiles) * (size_t)out * sizeof(double);
     return p;
 }
 
@@ -945,7 +1019,8 @@ int hscale_output_error(const void *X, int64_t tokens, int64_t in, const void *W
                        stream, static_cast<const u32x4 *>(W), out, in, global_scale, scale_codes,
                        reinterpret_cast<const uint2 *>(packed_e2m1), p.rows_pad, p.ldd, hi, lo, count, list);
     if (launch_status() != HSCALE_OK) return HSCALE_ERR_HIP;
-    const int64_t tile_tokens = gram ? kLfBM : p.tile_tokens;
+    const LfTile tile = gram ? kLfWide : p.tile;
+    const int64_t tile_tokens = kLfTiles[tile].tokens;
     int64_t pass_tiles = (int64_t)((direct_bytes - p.partial_offset) / ((size_t)out * sizeof(double)));
     if (pass_tiles > p.tiles_per_pass) pass_tiles = p.tiles_per_pass;
     const int64_t pass_tokens = pass_tiles * tile_tokens;
@@ -958,17 +1033,14 @@ int hscale_output_error(const void *X, int64_t tokens, int64_t in, const void *W
         a.lo = lo;
         a.ldd = p.ldd;
         a.out = out;
-        a.ntiles = p.ntiles;
+        a.ntiles = gram ? p.ntiles : p.row_tiles;
         a.partial = partial;
         a.count = count;
         const int64_t tiles = (a.tokens + tile_tokens - 1) / tile_tokens;
-        const dim3 grid((unsigned)(tiles * p.ntiles));
         if (gram)
             hipLaunchKernelGGL(lfull_listed_kernel, dim3(kListedBlocks), dim3(kLfThreads), 0, stream, a);
-        else if (tile_tokens == kLnBM)
-            hipLaunchKernelGGL(lfull_narrow_kernel, grid, dim3(kLnThreads), 0, stream, a);
         else
-            hipLaunchKernelGGL(lfull_tile_kernel, grid, dim3(kLfThreads), 0, stream, a);
+            launch_tiles(tile, tiles, stream, a);
         if (launch_status() != HSCALE_OK) return HSCALE_ERR_HIP;
         if (gram)
             hipLaunchKernelGGL(gram_fallback, dim3((unsigned)((out + 255) / 256)), dim3(256), 0, stream, partial, tiles,

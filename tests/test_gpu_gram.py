@@ -149,17 +149,19 @@ def test_squares_outside_fp32_go_direct(hs, scale):
     assert ((gram - plain).abs() <= 1e-12 * plain).all()
 
 
-# The direct route's two tiles: 128 tokens where those fill the CUs in fewer
-# rounds, 384 otherwise (the last case); edges of both, ragged rows and columns.
-@pytest.mark.parametrize("T,n,m", [(1, 16, 1), (127, 32, 255), (129, 48, 257), (385, 1040, 513), (2049, 528, 4100),
-                                   (4096, 256, 4096)])
+# The direct route's tiles, tokens x rows: 64 x 128 (the first five cases, of
+# 1, 1, 2, 3 and 33 stages), 128 x 128 (two), 128 x 256 (two), 256 x 256 (two)
+# and 384 x 256 (the last); edges, ragged rows and columns, more than a round.
+@pytest.mark.parametrize("T,n,m", [(1, 16, 1), (127, 32, 255), (129, 48, 257), (65, 80, 129), (385, 1040, 513),
+                                   (2945, 48, 1025), (3000, 96, 700), (2050, 16, 3900), (6500, 208, 700),
+                                   (2049, 528, 4100), (4096, 256, 4096), (5000, 80, 4096)])
 def test_direct_tiles_and_smaller_workspaces(hs, T, n, m):
     X, W = _case(T, n, m, seed=T + m)
     s_g, codes, packed = _stored(hs, W)
     ref = _reference(X, W, s_g, codes, packed)
     full = hs.output_error(X, W, s_g, codes, packed)
     least = torch.empty(_direct_bytes(T, n, m), dtype=torch.uint8, device=DEV)
-    passes = hs.output_error(X, W, s_g, codes, packed, workspace=least)  # narrow tiles in up to three passes
+    passes = hs.output_error(X, W, s_g, codes, packed, workspace=least)  # small tiles in several passes
     torch.cuda.synchronize()
     print(f"[direct {T}x{n}x{m}] max rel {_rel(full, ref):.2e}", flush=True)
     assert _rel(full, ref) <= REL_TOL
