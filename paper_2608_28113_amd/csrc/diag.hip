@@ -4,6 +4,8 @@
 
 #include "common.h"
 
+#include <algorithm>
+
 namespace {
 
 // ---------------------------------------------------------------------------
@@ -124,82 +126,110 @@ __global__ __launch_bounds__(kSumThreads) void shift_summary_partial(const int8_
     }
 }
 
-// The same for windows of few bins: every thread adds its 16 groups into sums
-// of its own in LDS (28 bytes per bin and thread, conflict-free whatever the
+// The same for windows of few bins: every thread adds its groups into sums of
+// its own in LDS (28 bytes per bin and thread, conflict-free whatever the
 // bins: a thread's slots lie in its own banks), each group once instead of
-// once per shift with a masked division.  Then 8 threads per sum add 32
-// threads' slots each, starting where no two lanes meet in a bank, and one
-// adds the 8.  3.67 M groups in 9 bins: 18 us, 35 us the other way.
-constexpr int kSumPrivateBins = 20;  // 140 KB of the CU's 160
+// once per shift with a masked division.  Then 8 threads per sum add an
+// eighth of the slots each, starting where no two lanes meet in a bank, and one
+// adds the 8.  As many blocks as are resident at once share the groups, so
+// the slots are cleared and summed once per CU and the next groups load while
+// these are added.  3.67 M groups with the final sum, in blocks of 4096 groups
+// before: 9 bins 16.8 us and 21.8, 17 bins 22 and 38; 24 bins 32 us, 73 the
+// other way.
+constexpr int kSumPrivateBins = 20;  // 140 KB of the CU's 160; twice as many with 128 threads
 constexpr int kSumParts = 8;
+constexpr int kSumBatch = 16;  // groups per thread and step
+constexpr size_t kSumBinBytes = 3 * sizeof(double) + sizeof(uint32_t);  // per thread
 
-__global__ __launch_bounds__(kSumThreads) void shift_summary_private(const int8_t *__restrict__ shift,
-                                                                     const float *__restrict__ err_best,
-                                                                     const float *__restrict__ err_init,
-                                                                     int64_t groups, int down, int up,
-                                                                     double *__restrict__ part,
-                                                                     uint32_t *__restrict__ cnt) {
+struct SumBatch {
+    int d[kSumBatch];
+    float best[kSumBatch], init[kSumBatch];
+};
+
+// Groups base, base + kThreads, ... below `to`.
+template <int kThreads>
+__device__ __forceinline__ void sum_load(SumBatch &v, const int8_t *__restrict__ shift,
+                                         const float *__restrict__ err_best, const float *__restrict__ err_init,
+                                         int64_t base, int64_t to) {
+#pragma unroll
+    for (int e = 0; e < kSumBatch; ++e) {
+        const int64_t g = base + e * kThreads;
+        const bool in = g < to;
+        v.d[e] = in ? (int)shift[g] : kSumOutside;
+        v.best[e] = in ? err_best[g] : 0.0f;
+        v.init[e] = in ? err_init[g] : 0.0f;
+    }
+}
+
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void shift_summary_private(const int8_t *__restrict__ shift,
+                                                                  const float *__restrict__ err_best,
+                                                                  const float *__restrict__ err_init,
+                                                                  int64_t groups, int64_t per_block, int down,
+                                                                  int up, double *__restrict__ part,
+                                                                  uint32_t *__restrict__ cnt) {
     extern __shared__ __attribute__((aligned(16))) uint8_t sums[];
     const int K = down + up + 1, tid = threadIdx.x;
-    double *val = reinterpret_cast<double *>(sums);                    // [3 K][kSumThreads]
-    uint32_t *num = reinterpret_cast<uint32_t *>(val + 3 * K * kSumThreads);  // [K][kSumThreads]
-    const int64_t base = (int64_t)blockIdx.x * kSumChunk + tid;
-    int d[kSumPerThread];
-    float eb[kSumPerThread], ei[kSumPerThread];
-#pragma unroll
-    for (int e = 0; e < kSumPerThread; ++e) {
-        const int64_t g = base + e * kSumThreads;
-        const bool in = g < groups;
-        d[e] = in ? (int)shift[g] : up + 1;
-        eb[e] = in ? err_best[g] : 0.0f;
-        ei[e] = in ? err_init[g] : 0.0f;
-    }
+    double *val = reinterpret_cast<double *>(sums);                    // [3 K][kThreads]
+    uint32_t *num = reinterpret_cast<uint32_t *>(val + 3 * K * kThreads);  // [K][kThreads]
+    int64_t base = (int64_t)blockIdx.x * per_block + tid;
+    const int64_t to = base - tid + per_block < groups ? base - tid + per_block : groups;
+    SumBatch v;
+    sum_load<kThreads>(v, shift, err_best, err_init, base, to);
     for (int k = 0; k < K; ++k) {
-        val[(3 * k) * kSumThreads + tid] = 0.0;
-        val[(3 * k + 1) * kSumThreads + tid] = 0.0;
-        val[(3 * k + 2) * kSumThreads + tid] = 0.0;
-        num[k * kSumThreads + tid] = 0u;
+        val[(3 * k) * kThreads + tid] = 0.0;
+        val[(3 * k + 1) * kThreads + tid] = 0.0;
+        val[(3 * k + 2) * kThreads + tid] = 0.0;
+        num[k * kThreads + tid] = 0u;
     }
+    while (base < to) {
+        const SumBatch now = v;
+        base += kSumBatch * kThreads;
+        sum_load<kThreads>(v, shift, err_best, err_init, base, to);
 #pragma unroll
-    for (int e = 0; e < kSumPerThread; ++e) {
-        if (d[e] < -down || d[e] > up) continue;
-        const int k = d[e] + down;
-        const double a = ei[e], b = eb[e];
-        double *v = val + 3 * k * kSumThreads + tid;
-        v[0] += a;
-        v[kSumThreads] += b;
-        v[2 * kSumThreads] += a > 0.0 ? (a - b) / a : 0.0;
-        num[k * kSumThreads + tid] += 1u;
+        for (int e = 0; e < kSumBatch; ++e) {
+            const double a = now.init[e], b = now.best[e];
+            const double rel = a > 0.0 ? (a - b) / a : 0.0;
+            if (now.d[e] < -down || now.d[e] > up) continue;
+            const int k = now.d[e] + down;
+            double *s = val + 3 * k * kThreads + tid;
+            s[0] += a;
+            s[kThreads] += b;
+            s[2 * kThreads] += rel;
+            num[k * kThreads + tid] += 1u;
+        }
     }
     __syncthreads();
-    // Sum p (three per bin, then the counts) in parts of 32 threads.  The
+    // Sum p (three per bin, then the counts) in parts of kPart threads.  The
     // parts' results replace the first slots of their ranges.
-    constexpr int kPart = kSumThreads / kSumParts;
-    for (int t = tid; t < 4 * K * kSumParts; t += kSumThreads) {
+    constexpr int kPart = kThreads / kSumParts;
+    for (int t = tid; t < 4 * K * kSumParts; t += kThreads) {
         const int p = t / kSumParts, from = t % kSumParts * kPart;
         if (p < 3 * K) {
-            double *v = val + p * kSumThreads + from;
+            double *v = val + p * kThreads + from;
             double s = 0.0;
+#pragma unroll
             for (int i = 0; i < kPart; ++i) s += v[(i + t) % kPart];
             v[0] = s;
         } else {
-            uint32_t *v = num + (p - 3 * K) * kSumThreads + from;
+            uint32_t *v = num + (p - 3 * K) * kThreads + from;
             uint32_t s = 0;
+#pragma unroll
             for (int i = 0; i < kPart; ++i) s += v[(i + t) % kPart];
             v[0] = s;
         }
     }
     __syncthreads();
-    for (int p = tid; p < 4 * K; p += kSumThreads) {
+    for (int p = tid; p < 4 * K; p += kThreads) {
         if (p < 3 * K) {
             double s = 0.0;
 #pragma unroll
-            for (int i = 0; i < kSumParts; ++i) s += val[p * kSumThreads + i * kPart];
+            for (int i = 0; i < kSumParts; ++i) s += val[p * kThreads + i * kPart];
             part[(size_t)blockIdx.x * K * 3 + p] = s;
         } else {
             uint32_t s = 0;
 #pragma unroll
-            for (int i = 0; i < kSumParts; ++i) s += num[(p - 3 * K) * kSumThreads + i * kPart];
+            for (int i = 0; i < kSumParts; ++i) s += num[(p - 3 * K) * kThreads + i * kPart];
             cnt[(size_t)blockIdx.x * K + p - 3 * K] = s;
         }
     }
@@ -920,7 +950,7 @@ int hscale_shift_summary(const int8_t *shift, const float *err_best, const float
     for (int a = 0; a < 4; ++a)
         for (int b = a + 1; b < 4; ++b)
             if (overlaps(outs[a], nk, outs[b], nk)) return HSCALE_ERR_OVERLAP;
-    const int64_t blocks = summary_blocks(groups);
+    int64_t blocks = summary_blocks(groups);
     const size_t need = hscale_shift_summary_workspace_bytes(groups, down, up);
     if (groups > 0) {
         if (!shift || !err_best || !err_init) return HSCALE_ERR_NULL;
@@ -939,13 +969,22 @@ int hscale_shift_summary(const int8_t *shift, const float *err_best, const float
         for (int a = 0; a < 3; ++a)
             if (overlaps(workspace, need, in_bufs[a].p, in_bufs[a].n)) return HSCALE_ERR_OVERLAP;
     }
+    const int private_threads = K <= kSumPrivateBins ? kSumThreads : K <= 2 * kSumPrivateBins ? kSumThreads / 2 : 0;
+    const size_t private_lds = (size_t)(K * private_threads) * kSumBinBytes;
+    if (private_threads)
+        blocks = std::min(blocks, std::min<int64_t>(8, (int64_t)(160 * 1024 / private_lds)) * 256);
     double *part = static_cast<double *>(workspace);
     uint32_t *cnt = blocks > 0 ? reinterpret_cast<uint32_t *>(part + (size_t)blocks * K * 3) : nullptr;
     if (blocks > 0) {
-        if (K <= kSumPrivateBins)
-            hipLaunchKernelGGL(shift_summary_private, dim3((unsigned)blocks), dim3(kSumThreads),
-                               (unsigned)(K * kSumThreads * (3 * sizeof(double) + sizeof(uint32_t))), stream, shift,
-                               err_best, err_init, groups, down, up, part, cnt);
+        const int64_t per_block = (groups + blocks - 1) / blocks;
+        if (private_threads == kSumThreads)
+            hipLaunchKernelGGL(shift_summary_private<kSumThreads>, dim3((unsigned)blocks), dim3(kSumThreads),
+                               (unsigned)private_lds, stream, shift, err_best, err_init, groups, per_block, down, up,
+                               part, cnt);
+        else if (private_threads)
+            hipLaunchKernelGGL(shift_summary_private<kSumThreads / 2>, dim3((unsigned)blocks), dim3(kSumThreads / 2),
+                               (unsigned)private_lds, stream, shift, err_best, err_init, groups, per_block, down, up,
+                               part, cnt);
         else
             hipLaunchKernelGGL(shift_summary_partial, dim3((unsigned)blocks), dim3(kSumThreads), 0, stream, shift,
                                err_best, err_init, groups, down, up, part, cnt);

@@ -300,10 +300,11 @@ def test_shift_summary_exact_groups_on_gpu(hs):
     assert np.array_equal(s["sum_rel"], rel)
 
 
-# Bins on both sides of the line (20) up to which each thread keeps sums of its
-# own; group counts around a block's 4096; shifts outside the window dropped.
-@pytest.mark.parametrize("down,up", [(0, 0), (4, 4), (9, 10), (10, 10), (125, 125)])
-@pytest.mark.parametrize("groups", [1, 4095, 4097, 20011])
+# Bins on both sides of the lines (20, and 40 with half the threads) up to which
+# each thread keeps sums of its own; group counts around a block's 4096, and
+# one that takes several steps of every block; shifts outside the window dropped.
+@pytest.mark.parametrize("down,up", [(0, 0), (4, 4), (9, 10), (10, 10), (20, 19), (20, 20), (125, 125)])
+@pytest.mark.parametrize("groups", [1, 4095, 4097, 20011, 2200003])
 def test_shift_summary_bins(hs, down, up, groups):
     rng = np.random.default_rng(groups + down)
     shift = rng.integers(max(-128, -down - 1), min(127, up + 1) + 1, groups).astype(np.int8)
@@ -320,6 +321,6 @@ def test_shift_summary_bins(hs, down, up, groups):
     assert np.array_equal(s["count"], np.bincount(d[keep], minlength=K))
     for key, v in (("sum_init", a), ("sum_best", b), ("sum_rel", rel)):
         want = np.bincount(d[keep], weights=v[keep], minlength=K)
-        # fp64 sums of at most 20011 non-negative terms in another order
-        assert np.all(np.abs(s[key] - want) <= 20011 * 2.0 ** -53 * want), key
+        # fp64 sums of `groups` non-negative terms in another order
+        assert np.all(np.abs(s[key] - want) <= groups * 2.0 ** -53 * want), key
     assert all(np.array_equal(s[k], again[k]) for k in s)
