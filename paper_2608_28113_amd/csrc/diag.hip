@@ -904,8 +904,8 @@ int gram_run(const GramPlan &gp, const LfPlan &p, const u32x4 *X, int64_t tokens
                            reinterpret_cast<uint2 *>(planes), reinterpret_cast<uint2 *>(planes + gp.plane_bytes));
         if (launch_status() != HSCALE_OK) return HSCALE_ERR_HIP;
     }
-    hipLaunchKernelGGL(gram_rows, dim3((unsigned)((out + 3) / 4)), dim3(256), 0, stream, W, out, in, s_g, codes, packed,
-                       diag, scale, (double)tokens, p.ldd, hi, lo, info, count);
+    hipLaunchKernelGGL(gram_rows, dim3((unsigned)((out + kGrRowBlock - 1) / kGrRowBlock)), dim3(kGrRowThreads), 0,
+                       stream, W, out, in, s_g, codes, packed, diag, scale, (double)tokens, p.ldd, hi, lo, info, count);
     if (launch_status() != HSCALE_OK) return HSCALE_ERR_HIP;
     GramApplyArgs g;
     g.g1 = reinterpret_cast<const u32x4 *>(planes);

@@ -8,7 +8,7 @@
 //                  block's four waves combine through LDS in a fixed order
 //                  and one fp64 partial per (slice, column) goes to the
 //                  caller's workspace.
-//   hdiag_small    the whole sum of at most 4096 tokens in one launch.
+//   hdiag_small    the whole sum of at most 1024 tokens in one launch.
 //   hdiag_tree     fixed-order fp64 sum of the slice partials, one fp32 h per
 //                  column (4, 16 or 64 lanes per column by slice count).  No atomics: results are bit-identical run to run.
 
