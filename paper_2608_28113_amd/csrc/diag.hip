@@ -883,6 +883,7 @@ int gram_run(const GramPlan &gp, const LfPlan &p, const u32x4 *X, int64_t tokens
     double *part = reinterpret_cast<double *>(ws + gp.part_offset);
     uint32_t *count = reinterpret_cast<uint32_t *>(ws + gp.list_offset);
     u32x4 *hi = reinterpret_cast<u32x4 *>(ws), *lo = reinterpret_cast<u32x4 *>(ws + p.plane_bytes);
+    const int least = gram_least_exponent(tokens);
     for (int64_t c0 = 0; c0 < gp.chunks; c0 += gp.pass_chunks) {
         const int64_t chunks = gp.chunks - c0 < gp.pass_chunks ? gp.chunks - c0 : gp.pass_chunks;
         const int64_t t0 = c0 * gp.chunk;
@@ -896,11 +897,11 @@ int gram_run(const GramPlan &gp, const LfPlan &p, const u32x4 *X, int64_t tokens
         hipLaunchKernelGGL(gram_kernel, dim3((unsigned)(chunks * gp.tri)), dim3(kGrThreads), 0, stream, a);
         if (launch_status() != HSCALE_OK) return HSCALE_ERR_HIP;
         hipLaunchKernelGGL(gram_diag, dim3((unsigned)gp.nt), dim3(kGrTile), 0, stream, partial, (int)gp.tri,
-                           (int)chunks, c0 == 0, diag, scale);
+                           (int)chunks, c0 == 0, least, diag, scale);
         if (launch_status() != HSCALE_OK) return HSCALE_ERR_HIP;
         hipLaunchKernelGGL(gram_reduce, dim3((unsigned)(gp.tri * (kGrUnitVecs / 256))), dim3(256), 0, stream, partial,
                            (int)gp.tri, (int)chunks, c0 == 0, c0 + chunks == gp.chunks,
-                           reinterpret_cast<double4 *>(ws + gp.g64_offset), gp.ldg, diag,
+                           reinterpret_cast<double4 *>(ws + gp.g64_offset), gp.ldg, diag, least,
                            reinterpret_cast<uint2 *>(planes), reinterpret_cast<uint2 *>(planes + gp.plane_bytes));
         if (launch_status() != HSCALE_OK) return HSCALE_ERR_HIP;
     }

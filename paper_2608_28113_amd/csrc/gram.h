@@ -9,7 +9,8 @@
 //   gram_kernel   fp32 partials of the lower-triangle tiles of G over token
 //                 chunks, on the matrix cores
 //   gram_diag     the diagonal of G in fp64, which also scales the rest: the
-//                 power of two 2^k_j next above sqrt(G_jj)
+//                 power of two 2^k_j next above sqrt(G_jj), or above what fp32
+//                 squares can hide of it
 //   gram_reduce   fp64 sum of the chunks; the off-diagonal G_ij / 2^(k_i + k_j)
 //                 (times two outside the diagonal tiles) as two f16 planes,
 //                 22 bits
@@ -204,15 +205,28 @@ __device__ __forceinline__ int gram_slot(int row, int col, int &component) {
     return ((wave * 8 + i * 2 + j) * 4 + e) * 64 + lane;
 }
 
-// k with 2^k the power of two next above sqrt(h) (0 for h = 0).
-__device__ __forceinline__ int channel_exponent(double h) {
-    return h > 0.0 && h < INFINITY ? (ilogb(h) + 2) >> 1 : 0;
+// k with 2^k the power of two next above sqrt(h), and no less than `least`:
+// squares below 2^-126 may count as zero in h, so a channel's true sum can be
+// up to tokens x 2^-126 larger, and 4^least covers that (gram_least_exponent).
+// An all-zero channel thereby gets a scale at the bottom of the range, where
+// its dW cannot outweigh that of live channels in gram_rows: a row that the
+// underflow check there lets pass has sqrt(D) >= |dW_rj| 2^(least + 10).
+__device__ __forceinline__ int channel_exponent(double h, int least) {
+    const int k = h > 0.0 && h < INFINITY ? (ilogb(h) + 2) >> 1 : least;
+    return k > least ? k : least;
+}
+
+// The smallest k with 4^k >= tokens x 2^-126.
+inline int gram_least_exponent(int64_t tokens) {
+    int k = -63;
+    for (int64_t t = 1; t < tokens; t *= 4) ++k;
+    return k;
 }
 
 // Diagonal of column tile blockIdx.x: the chunks' partials in chunk order, on
 // top of the earlier passes' sums, and the channels' 2^k.
 __global__ __launch_bounds__(kGrTile) void gram_diag(const float4 *__restrict__ partial, int tri, int chunks,
-                                                     bool first, double *__restrict__ diag,
+                                                     bool first, int least, double *__restrict__ diag,
                                                      float *__restrict__ scale) {
     const int x = threadIdx.x, J = blockIdx.x;
     int k;
@@ -222,7 +236,7 @@ __global__ __launch_bounds__(kGrTile) void gram_diag(const float4 *__restrict__ 
 #pragma unroll 8
     for (int c = 0; c < chunks; ++c) v += (double)src[(size_t)c * tri * kGrUnitVecs * 4];
     diag[J * kGrTile + x] = v;
-    scale[J * kGrTile + x] = ldexpf(1.0f, channel_exponent(v));
+    scale[J * kGrTile + x] = ldexpf(1.0f, channel_exponent(v, least));
 }
 
 // hi + lo of f in f16: 22 bits, and at least 2^-25 in absolute terms.
@@ -242,8 +256,8 @@ constexpr int kGrPlaneExp = 10;
 // when `first`, not written when `last`).  The last pass writes the planes.
 __global__ __launch_bounds__(256) void gram_reduce(const float4 *__restrict__ partial, int tri, int chunks,
                                                    bool first, bool last, double4 *__restrict__ g64, int64_t ldg,
-                                                   const double *__restrict__ diag, uint2 *__restrict__ g1,
-                                                   uint2 *__restrict__ g2) {
+                                                   const double *__restrict__ diag, int least,
+                                                   uint2 *__restrict__ g1, uint2 *__restrict__ g2) {
     const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int q = (int)(blockIdx.x / (kGrUnitVecs / 256));
     const int f = (int)(id % kGrUnitVecs);
@@ -267,11 +281,11 @@ __global__ __launch_bounds__(256) void gram_reduce(const float4 *__restrict__ pa
     gram_tile(q, I, J);
     const int64_t row = (int64_t)I * kGrTile + (wave & 1) * 128 + i * 32 + 8 * e + 4 * (lane >> 5);
     const int64_t col = (int64_t)J * kGrTile + (wave >> 1) * 64 + j * 32 + (lane & 31);
-    const int weight = kGrPlaneExp + (I == J ? 0 : 1) - channel_exponent(diag[col]);
+    const int weight = kGrPlaneExp + (I == J ? 0 : 1) - channel_exponent(diag[col], least);
     uint32_t a[4], b[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        const double gv = row + k == col ? 0.0 : ldexp(v[k], weight - channel_exponent(diag[row + k]));
+        const double gv = row + k == col ? 0.0 : ldexp(v[k], weight - channel_exponent(diag[row + k], least));
         split_f16((float)gv, a[k], b[k]);
     }
     const int64_t at = (col * ldg + row) / 4;  // plane row = column of the tile: rows run along k
