@@ -31,17 +31,27 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 // gram_kernel: a 256 x 256 tile of G per block, 8 waves of 128 x 64, two per
 // SIMD.  The matrix cores bound it (75% busy, at the 1.6 GHz that this load
 // runs at): at 262144 tokens of 4096 columns it takes 3.7 ms = 1.27 PFLOP/s
-// issued.  What mattered: reads of the next 16-token step interleaved with
-// the MFMAs of the current one, two reads to an MFMA (4.3 ms without, 65%
-// busy); 128 x 128 per wave at one wave per SIMD reads a third less LDS but
-// took 4.4 to 4.8 ms.  64 tokens per stage put 32 MFMAs of a wave between two
-// barriers.
+// issued in chunks of 17500 tokens.  What mattered: reads of the next 16-token
+// step interleaved with the MFMAs of the current one, two reads to an MFMA
+// (4.3 ms without, 65% busy); 128 x 128 per wave at one wave per SIMD reads a
+// third less LDS but took 4.4 to 4.8 ms.  64 tokens per stage put 32 MFMAs of
+// a wave between two barriers.
 constexpr int kGrTile = 256;
 constexpr int kGrThreads = 512;
 constexpr int kGrBK = 64;                            // tokens per stage
 constexpr int kGrOpBytes = kGrBK * kGrTile * 2;      // one operand's stage
 constexpr int kGrUnitVecs = kGrTile * kGrTile / 4;   // float4 of a tile's partial
-constexpr int kGrChunkTokens = 18432;                // tokens of one fp32 chain, about
+// Tokens of one fp32 chain, at most: the direct product sums over tokens in
+// fp64, and where tokens repeat (padding, a constant channel) every addition
+// of a binade rounds the same way, so the error of a chain grows with its
+// length.  At 262144 x 4096 with 4096 rows, half of the tokens one token: of a
+// row's sum up to 2.1e-4 in chains of 17500 tokens, 1.8e-5 of 4096, 3.2e-6 of
+// 2048 (direct: 1.2e-5); two tokens in turn, on average 3.4e-5, 8.4e-6 and
+// 3.3e-6 (direct: 4.6e-6).  The partials of short chains cost traffic: with
+// 14336 rows 4.6 ms, 5.1, 5.8, and 7.6 with chains of 1024.  Adding each
+// accumulator to the block's partial every 2048 tokens instead of ending the
+// chunk took 6.0 ms.
+constexpr int kGrChunkTokens = 2048;
 constexpr int kGrMinChunk = 1024;
 constexpr int64_t kGrMaxUnits = 4608;  // partial tiles per pass (1.2 GB of workspace)
 constexpr int64_t kGrMaxTiles = 64;    // in <= 16384
@@ -555,12 +565,18 @@ __global__ __launch_bounds__(kGrThreads, 2) void gram_apply(const GramApplyArgs 
     if (tid < kGrTile && r0 + tid < a.out) a.part[jt * a.out + r0 + tid] = red[tid] + red[kGrTile + tid];
 }
 
-// A row's Gram sum L = D + E carries rounding errors of about 4e-7 D, whatever
-// L is (measured up to 8e-7 D where few channels dominate), while the direct
-// product's, up to 1.2e-5 L there, follow L.  Rows whose off-diagonal part
-// cancels D to below 1/16 are left to the direct product, and so are rows
-// that overflowed on the way or whose D says NaN.
-constexpr double kGrCancel = 0x1p-4;
+// A row's Gram sum L = D + E carries rounding errors that follow D, whatever
+// L is: about 4e-7 D (up to 8e-7 D where few channels dominate), and up to
+// 6e-6 D where one or two tokens are all there is.  The direct product's, up
+// to 1.2e-5 sqrt(D L), follow L too.  Rows whose off-diagonal part cancels D
+// to below 1/4 are left to the direct product, and so are rows that
+// overflowed on the way or whose D says NaN (262144 x 4096 of two tokens in
+// turn, largest error of the other rows against the direct product's: 1e-4
+// against 5e-5 with the line at 1/16, 5e-5 and 3e-5 at 1/8, 2.9e-5 and 2.5e-5
+// at 1/4).  Listed rows take the direct product's time on top: none where the
+// activations have many directions, but 38% of the rows (a squared normal
+// below 1/4) where one direction that many channels share makes up X^T X.
+constexpr double kGrCancel = 0x1p-2;
 
 __global__ __launch_bounds__(256) void gram_finish(const GramRow *__restrict__ info, const double *__restrict__ part,
                                                    int column_tiles, int64_t out, double *__restrict__ row_err,
@@ -594,16 +610,19 @@ struct GramPlan {
     bool use = false;
     int64_t nt = 0, tri = 0, ldg = 0;
     int64_t chunk = 0, chunks = 0, pass_chunks = 0;
-    size_t partial_offset = 0, g64_offset = 0, plane_offset = 0, plane_bytes = 0, diag_offset = 0, scale_offset = 0, info_offset = 0,
-           part_offset = 0, list_offset = 0, bytes = 0;
+    size_t partial_offset = 0, g64_offset = 0, plane_offset = 0, plane_bytes = 0;
+    size_t diag_offset = 0, scale_offset = 0, info_offset = 0, part_offset = 0, list_offset = 0, bytes = 0;
 };
 
 // The Gram route's plan, behind the direct route's workspace of `base` bytes.
-// It is used where its estimated time (matrix-core flops at the rates both
-// routes measured, the partials' traffic and a fixed cost) is at most 0.85 of
-// the direct product's: n^2 T against 4 n m T, so from about m = n / 3 up for
-// long calibration sets (262144 x 4096 against 14336 rows: 4.9 ms, direct
-// 45.8 ms).
+// It is used where its estimated time (matrix-core flops and traffic of the
+// partials at the rates measured, and a fixed cost; within 7% from 845 us to
+// 6.8 ms) is at most 0.6 of the direct product's: n^2 T against 4 n m T, so
+// from about m = 0.7 n up for long calibration sets (262144 x 4096 against
+// 14336 rows: 5.8 ms, direct 45.8 ms).  The 0.6 leaves the direct product of
+// the 38% of rows that may have to be listed (kGrCancel) within about the
+// direct route's time (such X, with 14336 rows 24.5 ms against 46.1; 65536 x
+// 2048 with 2048 rows, near the line, 0.50 ms or 0.96 against 0.85).
 GramPlan gram_plan(int64_t tokens, int64_t in, int64_t out, int64_t ldd, int64_t rows_pad, size_t base) {
     GramPlan p;
     if (tokens <= 0 || in <= 0 || out <= 0) return p;
@@ -611,30 +630,39 @@ GramPlan gram_plan(int64_t tokens, int64_t in, int64_t out, int64_t ldd, int64_t
     if (p.nt > kGrMaxTiles || out > ((int64_t)1 << 28)) return p;  // rows are listed in 32 bits
     p.tri = p.nt * (p.nt + 1) / 2;
     p.ldg = p.nt * kGrTile;
-    // Chunks: chains of at most about kGrChunkTokens, and at least four rounds
-    // of blocks where the tokens allow; of the counts up to twice that, the
+    // Chunks: chains of at most kGrChunkTokens, and at least four rounds of
+    // blocks where the tokens allow; of the counts up to twice that, the
     // smallest (least partials traffic) whose rounds of 256 blocks are within
-    // 2% of the fullest.
+    // 2% of the fullest.  As few passes as the partials' share of the
+    // workspace allows, of equal size.
+    const int64_t cap = kGrMaxUnits / p.tri;
+    auto per_pass = [&](int64_t s) {
+        const int64_t passes = (s + cap - 1) / cap;
+        return (s + passes - 1) / passes;
+    };
     int64_t lo = (tokens + kGrChunkTokens - 1) / kGrChunkTokens;
     const int64_t fill = (1024 + p.tri - 1) / p.tri, most = (tokens + kGrMinChunk - 1) / kGrMinChunk;
     if (lo < fill) lo = fill < most ? fill : most;
     const int64_t hi = 2 * lo < most ? 2 * lo : most, end = hi < lo + 64 ? hi : lo + 64;
-    auto rounds = [&](int64_t s) { return (double)((s * p.tri + 255) / 256) / (double)s; };
+    auto rounds = [&](int64_t s) {  // a chunk's share
+        const int64_t per = per_pass(s), full = s / per, rest = s % per;
+        return (double)(full * ((per * p.tri + 255) / 256) + (rest * p.tri + 255) / 256) / (double)s;
+    };
     double fullest = rounds(lo);
     for (int64_t s = lo; s <= end; ++s) fullest = rounds(s) < fullest ? rounds(s) : fullest;
     int64_t best = lo;
     while (rounds(best) > 1.02 * fullest) ++best;
     p.chunk = (int64_t)round_up((size_t)((tokens + best - 1) / best), kGrBK);
     p.chunks = (tokens + p.chunk - 1) / p.chunk;
-    const int64_t cap = kGrMaxUnits / p.tri;
-    p.pass_chunks = p.chunks < cap ? p.chunks : cap;
+    p.pass_chunks = per_pass(p.chunks);
 
     const double T = (double)tokens, m = (double)rows_pad, n = (double)ldd;
     const double direct = 4.0 * T * n * m / 1.3e15;
     const double units = (double)p.chunks * (double)p.tri;
-    const double gram = 131072.0 * (double)p.tri * T / 1.1e15 + 6.0 * m * 65536.0 * (double)p.tri / 1.1e15 +
-                        units * kGrUnitVecs * 32.0 / 4e12 + 100e-6;
-    if (gram > 0.85 * direct) return p;
+    const double carried = p.pass_chunks < p.chunks ? (double)((p.chunks + p.pass_chunks - 1) / p.pass_chunks) : 0.0;
+    const double gram = 131072.0 * (double)p.tri * T / 1.2e15 + 6.0 * m * 65536.0 * (double)p.tri / 1.1e15 +
+                        (units * 32.0 + carried * (double)p.tri * 64.0) * kGrUnitVecs / 7e12 + 100e-6;
+    if (gram > 0.6 * direct) return p;
     p.use = true;
     p.plane_bytes = (size_t)p.ldg * (size_t)p.ldg * 2;
     p.partial_offset = round_up(base, 256);

@@ -139,6 +139,33 @@ def test_cancelling_rows_lose_no_precision(hs, noise):
         assert ((gram[even] - plain[even]).abs() <= 1e-12 * plain[even]).all()  # the direct sums, in another order
 
 
+@pytest.mark.parametrize("kind", ["padding", "two tokens", "constant channels"])
+def test_repeated_tokens_lose_no_precision(hs, kind):
+    """Equal tokens add with equal rounding, so a long fp32 chain over them
+    drifts, where the direct product sums over tokens in float64.  Of the rows
+    that the Gram route answers itself, the error as a whole and on average is
+    no larger than the direct product's.  So is the largest but for chance:
+    one row that cancels to just above the line decides it on either side."""
+    X, W = _case(147456, 4096, 4096, seed=3)
+    T = X.shape[0]
+    if kind == "padding":
+        X[T // 2:] = X[5].clone()
+    elif kind == "two tokens":
+        X[:] = X[:2].repeat(T // 2, 1)
+    else:
+        X[:, ::2] = X[3, ::2].clone()
+    s_g, codes, packed = _stored(hs, W)
+    gram, plain = _both(hs, X, W, s_g, codes, packed)
+    ref = _reference(X, W, s_g, codes, packed)
+    own = (gram - plain).abs() > 1e-12 * plain
+    g, d = (((v - ref).abs() / ref)[own] for v in (gram, plain))
+    print(f"  {kind}: own rows {own.float().mean().item():.3f} max {g.max().item():.2e} direct {d.max().item():.2e}; "
+          f"mean {g.mean().item():.2e} {d.mean().item():.2e}; norm {((gram - ref).norm() / ref.norm()).item():.2e} "
+          f"{((plain - ref).norm() / ref.norm()).item():.2e}", flush=True)
+    assert (gram - ref).norm() <= (plain - ref).norm()
+    assert g.mean() <= d.mean() and g.max() <= 1.5 * d.max()
+
+
 # Channels that are zero, or whose squares underflow fp32, beside live ones: the
 # scales of the 16-bit planes must not depend on them.  Rows of this input do
 # not cancel, and without such channels the largest relative error is 2e-7 at
