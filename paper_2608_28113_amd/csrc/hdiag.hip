@@ -367,7 +367,12 @@ const char *hscale_status_string(int status) {
 
 size_t hscale_hdiag_workspace_bytes(int64_t tokens, int64_t in) {
     if (tokens <= 0 || in <= 0 || in % kGroup != 0) return 0;
-    return hdiag_bytes(hdiag_plan(tokens, in, false), in);
+    // At least the coarse plan's: slices moved off a spacing can be fewer, and
+    // a buffer sized for a full batch also serves a shorter last one, whose
+    // slices may not be moved.
+    const size_t fine = hdiag_bytes(hdiag_plan(tokens, in, false), in);
+    const size_t coarse = hdiag_bytes(hdiag_plan(tokens, in, true), in);
+    return fine > coarse ? fine : coarse;
 }
 
 int hscale_hdiag(const void *X, int64_t tokens, int64_t in, float *h, void *workspace, size_t workspace_bytes,

@@ -57,6 +57,22 @@ def test_workspace_bytes(L):
         assert b <= 0.02 * 2 * T * n or T * n < 1 << 20  # partials are a small fraction of X
 
 
+def test_hdiag_workspace_serves_shorter_batches(L):
+    """The size covers slices of at least 256 tokens over the resident grid,
+    whatever plan is taken, so that a buffer sized for a full batch is enough
+    for every shorter one of at least as many columns' partials."""
+    def coarse(T, n):
+        slices = max(1, min(1792 // -(-n // 512), -(-T // 256)))
+        return -(-T // -(-T // slices)) * n * 8
+
+    for n in (16, 512, 528, 2048, 4096, 8192, 12288, 14336, 16384, 28672):
+        for T in (1, 256, 1024, 1025, 2048, 4096, 8192, 16384, 16385, 32768, 65536, 262144):
+            need = L.hscale_hdiag_workspace_bytes(T, n)
+            assert need >= coarse(T, n), (T, n)
+    # 64 slices of 256 tokens start 2 MB apart and become 57; 16129 tokens keep 64 of 253
+    assert L.hscale_hdiag_workspace_bytes(16384, 4096) >= L.hscale_hdiag_workspace_bytes(16129, 4096)
+
+
 # Fake but aligned device addresses: validation never dereferences them.
 A = 1 << 20
 

@@ -41,3 +41,18 @@ def test_hdiag_plans(hs, T, n):
         assert rel <= 2e-6  # chains of at most 32 fp32 additions: 31.5 x 2^-24
     assert torch.equal(h, h_acc)
     assert torch.equal(h, hs.hdiag(X))
+
+
+@pytest.mark.parametrize("full,last,n", [(16384, 16129, 4096), (8192, 8065, 8192), (4096, 3841, 16384)])
+def test_a_workspace_for_a_full_batch_serves_the_last_one(hs, full, last, n):
+    """Slices of the full batch are moved off a 2 MB spacing and fewer than
+    the shorter batch's."""
+    ws = torch.empty(hs.hdiag_workspace_bytes(full, n), dtype=torch.uint8, device=DEV)
+    X = torch.randn((full, n), generator=torch.Generator(device=DEV).manual_seed(n), device=DEV).bfloat16()
+    for T in (full, last):
+        h = hs.hdiag(X[:T], workspace=ws)
+        ref = X[:T].double().square_().sum(0)
+        torch.cuda.synchronize()
+        print(f"[{T}x{n}] workspace {ws.numel()}, asked for {hs.hdiag_workspace_bytes(T, n)}", flush=True)
+        assert ((h.double() - ref).abs() <= 2e-6 * ref).all()
+        assert torch.equal(h, hs.hdiag(X[:T]))
