@@ -8,7 +8,7 @@
 //                  block's four waves combine through LDS in a fixed order
 //                  and one fp64 partial per (slice, column) goes to the
 //                  caller's workspace.
-//   hdiag_small    the whole sum of at most 1024 tokens in one launch.
+//   hdiag_small    the whole sum of few tokens (hdiag_one_launch) in one launch.
 //   hdiag_tree     fixed-order fp64 sum of the slice partials, one fp32 h per
 //                  column (4, 16 or 64 lanes per column by slice count).  No atomics: results are bit-identical run to run.
 
@@ -41,6 +41,21 @@ constexpr int kHdTargetBlocks = 1792;
 // to the smaller number with 16 rows at once in blocks of 256 threads.
 constexpr int64_t kHdSmallTokens = 1024;
 constexpr int64_t kHdFewTokens = 256;
+// Above kHdFewTokens its blocks of 64 columns and 1024 threads read 128 bytes
+// of a row each, which pays while every CU has at most one (257 to 1024
+// tokens x 16384 columns 5.1 to 7.7 us, in two launches 7.4 to 11.0), and with
+// two in the middle of the range (28672 columns: 320 tokens 8.0 against 8.4,
+// 512 8.3 against 10.9, 900 11.2 against 11.4, but 257 7.8 both, 1024 12.4
+// against 12.2); beyond that it loses (57344 columns: 257 tokens 13.0 against
+// 8.4, 512 14.2 against 12.3, 1024 23.2 against 20.3).
+constexpr int64_t kHdSmallCols = 16384;
+constexpr int64_t kHdTwiceMinTokens = 320, kHdTwiceMaxTokens = 896;
+// Up to kHdFewTokens a block reads 256 bytes of 16 rows at once, which leaves
+// lanes idle below 16 rows: no loss while launches bound the call (262144
+// columns: 1 token 5.7 us, in two launches 6.6; 16 tokens 6.7 and 6.9), but
+// with 1048576 columns 18.0 against 14.1 and 19.7 against 18.0 (64 tokens 22.5
+// against 44.1).
+constexpr int64_t kHdFewCols = 262144, kHdFewMinTokens = 64;
 // Slices of 256 tokens or more; where those give fewer than 192 blocks,
 // shorter ones (down to one batch of loads per lane) for 512 blocks: their
 // partials cost up to 25% of X's traffic, an idle CU more.  Measured, both
@@ -72,7 +87,7 @@ HdiagPlan hdiag_plan(int64_t tokens, int64_t in, bool coarse) {
     const int64_t resident = kHdTargetBlocks / p.tiles;
     int64_t slices = (tokens + kHdSliceTokens - 1) / kHdSliceTokens;
     if (slices > resident) slices = resident;
-    const bool fine = !coarse && tokens > kHdSmallTokens;  // hdiag_small uses no partials
+    const bool fine = !coarse && tokens > kHdSmallTokens;
     if (slices < 1) slices = 1;
     p.slice_tokens = (tokens + slices - 1) / slices;
     if (fine) {
@@ -86,6 +101,13 @@ HdiagPlan hdiag_plan(int64_t tokens, int64_t in, bool coarse) {
     }
     p.slices = (tokens + p.slice_tokens - 1) / p.slice_tokens;
     return p;
+}
+
+// Whether hdiag_small takes it.
+bool hdiag_one_launch(int64_t tokens, int64_t in) {
+    if (tokens <= kHdFewTokens) return in <= kHdFewCols || tokens >= kHdFewMinTokens;
+    return (tokens <= kHdSmallTokens && in <= kHdSmallCols) ||
+           (tokens >= kHdTwiceMinTokens && tokens <= kHdTwiceMaxTokens && in <= 2 * kHdSmallCols);
 }
 
 size_t hdiag_bytes(const HdiagPlan &p, int64_t in) { return (size_t)p.slices * (size_t)in * sizeof(double); }
@@ -285,7 +307,7 @@ int hdiag_run(const void *X, int64_t tokens, int64_t in, float *h, double *h64, 
         if (!aligned(workspace, 16)) return HSCALE_ERR_ALIGN;
         const size_t nx = (size_t)tokens * (size_t)in * 2;
         if (overlaps(workspace, need, X, nx) || overlaps(workspace, need, out, nout)) return HSCALE_ERR_OVERLAP;
-        if (tokens <= kHdSmallTokens) {
+        if (hdiag_one_launch(tokens, in)) {
             if (tokens <= kHdFewTokens)
                 launch_small<256, 16>(X, tokens, in, h, h64, stream);
             else

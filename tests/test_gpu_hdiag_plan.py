@@ -1,5 +1,5 @@
 """hdiag at the edges of its plans: one launch for few tokens (16 rows at once
-up to 256 tokens, 128 rows up to 1024), short slices, slices moved off a
+up to 256 tokens, 128 rows up to 1024 of few columns), short slices, slices moved off a
 2 MB spacing, and the coarse slices of a smaller workspace."""
 from __future__ import annotations
 
@@ -20,7 +20,8 @@ def hs():
 
 @pytest.mark.parametrize("T,n", [(1, 16), (15, 112), (128, 512), (256, 144), (257, 64), (1024, 1040), (1025, 1040),
                                  (1056, 4096), (2040, 4096), (4095, 528), (2048, 14336), (8192, 4096), (8193, 8192),
-                                 (65537, 48)])
+                                 (65537, 48), (300, 16384), (300, 16400), (319, 32768), (320, 32768), (320, 32784),
+                                 (896, 20480), (897, 20480), (3, 262144), (3, 262160), (64, 262160)])
 def test_hdiag_plans(hs, T, n):
     g = torch.Generator(device=DEV).manual_seed(T * 31 + n)
     X = (torch.randn((T, n), generator=g, device=DEV) * torch.exp(torch.randn(n, generator=g, device=DEV))).bfloat16()
@@ -56,3 +57,21 @@ def test_a_workspace_for_a_full_batch_serves_the_last_one(hs, full, last, n):
         print(f"[{T}x{n}] workspace {ws.numel()}, asked for {hs.hdiag_workspace_bytes(T, n)}", flush=True)
         assert ((h.double() - ref).abs() <= 2e-6 * ref).all()
         assert torch.equal(h, hs.hdiag(X[:T]))
+
+
+def test_hdiag_of_very_many_columns(hs):
+    """Blocks of 64 columns and 1024 threads would make a grid of 2^32
+    threads, which no launch takes."""
+    T, n = 257, 1 << 28
+    if torch.cuda.mem_get_info()[0] < 160 << 30:
+        pytest.skip("needs 160 GB of free GPU memory")
+    X = torch.zeros((T, n), dtype=torch.bfloat16, device=DEV)
+    cols = torch.tensor([0, 12345, n // 2 + 7, n - 1], device=DEV)
+    X[:, cols] = 0.5
+    print(f"[{T}x{n}]", flush=True)
+    h = hs.hdiag(X)
+    torch.cuda.synchronize()
+    assert torch.equal(h[cols], torch.full((4,), T * 0.25, device=DEV))
+    assert int(torch.count_nonzero(h)) == 4
+    del X, h
+    torch.cuda.empty_cache()
