@@ -71,6 +71,11 @@ constexpr int64_t kHdFewBlocks = 192, kHdEnoughBlocks = 512;
 // 4096 columns at 16384 tokens: 37.1 us, 25.5 with the 32 more; at 32768 62.1
 // and 47.1; with 8192 columns at 8192 tokens 33.8 and 26.2.  Slices 1, 2.5 or
 // 3.5 MB apart (2048, 5120 and 14336 columns) gain nothing, and lose 1-3%.
+// Rows of more than 32 KB spread over the channels by themselves: 24576
+// columns at 2048 tokens take 18.6 us as they are and 20.0 with more slices,
+// 28672 at 4096 41.1 and 43.0, 57344 at 2048 39.8 and 42.8; up to 16384 columns
+// all gain (4096 tokens 29.6 and 23.7).
+constexpr int64_t kHdAliasCols = 16384;
 constexpr int64_t kHdAlias = ((int64_t)2 << 20) / 2;  // in elements
 constexpr int64_t kHdLongSliceTokens = 1024;
 
@@ -91,7 +96,9 @@ HdiagPlan hdiag_plan(int64_t tokens, int64_t in, bool coarse) {
     if (slices < 1) slices = 1;
     p.slice_tokens = (tokens + slices - 1) / slices;
     if (fine) {
-        auto aliased = [&] { return p.slice_tokens < kHdLongSliceTokens && p.slice_tokens * in % kHdAlias == 0; };
+        auto aliased = [&] {
+            return in <= kHdAliasCols && p.slice_tokens < kHdLongSliceTokens && p.slice_tokens * in % kHdAlias == 0;
+        };
         if (slices * p.tiles < (aliased() ? kHdEnoughBlocks : kHdFewBlocks)) {
             slices = (kHdEnoughBlocks + p.tiles - 1) / p.tiles;
             p.slice_tokens = (tokens + slices - 1) / slices;

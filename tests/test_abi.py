@@ -69,6 +69,9 @@ def test_hdiag_workspace_serves_shorter_batches(L):
         for T in (1, 256, 1024, 1025, 2048, 4096, 8192, 16384, 16385, 32768, 65536, 262144):
             need = L.hscale_hdiag_workspace_bytes(T, n)
             assert need >= coarse(T, n), (T, n)
+    # rows beyond 32 KB need no slices off a spacing, and get no more of them
+    for n in (20480, 24576, 28672):
+        assert L.hscale_hdiag_workspace_bytes(2048, n) == coarse(2048, n), n
     # 64 slices of 256 tokens start 2 MB apart and become 57; 16129 tokens keep 64 of 253
     assert L.hscale_hdiag_workspace_bytes(16384, 4096) >= L.hscale_hdiag_workspace_bytes(16129, 4096)
 
