@@ -55,6 +55,7 @@ constexpr int kGrChunkTokens = 2048;
 constexpr int kGrMinChunk = 1024;
 constexpr int64_t kGrMaxUnits = 4608;  // partial tiles per pass (1.2 GB of workspace)
 constexpr int64_t kGrMaxTiles = 64;    // in <= 16384
+constexpr int64_t kGrMaxOut = (int64_t)1 << 25;  // gram_rows' grid: 64 threads a row, below 2^32 in all
 constexpr uint32_t kGrOutside = 0x7FFF0000u;  // beyond every descriptor's range
 
 struct GramArgs {
@@ -627,7 +628,7 @@ GramPlan gram_plan(int64_t tokens, int64_t in, int64_t out, int64_t ldd, int64_t
     GramPlan p;
     if (tokens <= 0 || in <= 0 || out <= 0) return p;
     p.nt = (in + kGrTile - 1) / kGrTile;
-    if (p.nt > kGrMaxTiles || out > ((int64_t)1 << 28)) return p;  // rows are listed in 32 bits
+    if (p.nt > kGrMaxTiles || out > kGrMaxOut) return p;
     p.tri = p.nt * (p.nt + 1) / 2;
     p.ldg = p.nt * kGrTile;
     // Chunks: chains of at most kGrChunkTokens, and at least four rounds of

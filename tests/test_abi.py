@@ -123,6 +123,16 @@ def test_hdiag_noalloc_validation(L):
     assert L.status_string(-10).startswith("HSCALE_ERR_DEVICE")
 
 
+def test_output_error_of_very_many_rows_goes_direct(L):
+    """The other route has 64 threads to a row in one launch of at most 2^32."""
+    T, n = 8000, 16
+    for m in (1 << 26, 1 << 27):
+        direct = 2 * m * 32 * 2 + -(-T // 384) * m * 8
+        assert L.hscale_output_error_workspace_bytes(T, n, m) == direct, m
+    m = 1 << 25
+    assert L.hscale_output_error_workspace_bytes(T, n, m) > 2 * m * 32 * 2 + -(-T // 384) * m * 8
+
+
 def test_search_validation(L):
     m, n = 4, 64
     W, h, codes, packed = A, 2 * A, 3 * A, 4 * A

@@ -210,3 +210,24 @@ def test_direct_tiles_and_smaller_workspaces(hs, T, n, m):
     print(f"[direct {T}x{n}x{m}] max rel {_rel(full, ref):.2e}", flush=True)
     assert _rel(full, ref) <= REL_TOL
     assert ((full - passes).abs() <= 1e-12 * full).all()
+
+
+def test_very_many_rows(hs):
+    """2^26 rows, more than one launch of the other route's row kernel holds."""
+    T, n, m = 8000, 16, 1 << 26
+    if torch.cuda.mem_get_info()[0] < 64 << 30:
+        pytest.skip("needs 64 GB of free GPU memory")
+    X, _ = _case(T, n, 16, seed=8)
+    W = torch.zeros((m, n), dtype=torch.bfloat16, device=DEV)
+    rows = torch.tensor([0, 4099, m // 2 + 1, m - 1], device=DEV)
+    W[rows] = (0.02 * torch.randn((4, n), generator=torch.Generator(device=DEV).manual_seed(9), device=DEV)).bfloat16()
+    codes = torch.zeros((m, 1), dtype=torch.uint8, device=DEV)  # scale 0: dW = W
+    packed = torch.zeros((m, n // 2), dtype=torch.uint8, device=DEV)
+    print(f"[direct {T}x{n}x{m}]", flush=True)
+    L = hs.output_error(X, W, 1.0, codes, packed)
+    torch.cuda.synchronize()
+    ref = (X.double() @ W[rows].double().t().contiguous()).square_().sum(0)
+    assert _rel(L[rows], ref) <= REL_TOL
+    assert int(torch.count_nonzero(L)) == 4
+    del W, codes, packed, L
+    torch.cuda.empty_cache()
