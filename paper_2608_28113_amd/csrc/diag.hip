@@ -830,6 +830,7 @@ struct LfPlan {
     LfTile tile = kLfWide;
     int64_t tile_tokens = 0, row_tiles = 0;  // of the chosen tile
     int64_t tiles_per_pass = 0;              // token tiles of a pass
+    int64_t wide_per_pass = 0;               // the same with kLfWide tiles
     size_t plane_bytes = 0, partial_offset = 0;
     size_t least = 0, bytes = 0;  // smallest workspace accepted, and the one asked for
 };
@@ -856,9 +857,10 @@ LfPlan lfull_plan(int64_t tokens, int64_t in, int64_t out) {
     p.plane_bytes = round_up((size_t)p.rows_pad * (size_t)p.ldd * 2, 256);
     p.partial_offset = 2 * p.plane_bytes;
     p.bytes = p.partial_offset + (size_t)p.tiles_per_pass * (size_t)out * sizeof(double);
-    // The partials of large tiles are enough: smaller ones then take more
-    // passes.
-    p.least = p.partial_offset + (size_t)capped((tokens + kLfBM - 1) / kLfBM, p.ntiles) * (size_t)out * sizeof(double);
+    // The partials of the largest tiles are enough, which are then taken:
+    // smaller ones would need several passes, each too small for the chip.
+    p.wide_per_pass = capped((tokens + kLfBM - 1) / kLfBM, p.ntiles);
+    p.least = p.partial_offset + (size_t)p.wide_per_pass * (size_t)out * sizeof(double);
     return p;
 }
 
@@ -1033,10 +1035,9 @@ int hscale_output_error(const void *X, int64_t tokens, int64_t in, const void *W
     };
     if (hits(p.least)) return HSCALE_ERR_OVERLAP;
     // What a larger workspace adds is used where it is there and overlaps no
-    // buffer: the partials of the direct product's tiles in fewer passes, and
-    // the Gram route.
-    size_t direct_bytes = workspace_bytes < p.bytes ? workspace_bytes : p.bytes;
-    if (hits(direct_bytes)) direct_bytes = p.least;
+    // buffer: the partials of the direct product's smaller tiles, and the Gram
+    // route.
+    const bool small_tiles = workspace_bytes >= p.bytes && !hits(p.bytes);
     const GramPlan gp = gram_plan(tokens, in, out, p.ldd, p.rows_pad, p.bytes);
     const bool gram = gp.use && workspace_bytes >= gp.bytes && !hits(gp.bytes);
 
@@ -1059,11 +1060,9 @@ int hscale_output_error(const void *X, int64_t tokens, int64_t in, const void *W
                        stream, static_cast<const u32x4 *>(W), out, in, global_scale, scale_codes,
                        reinterpret_cast<const uint2 *>(packed_e2m1), p.rows_pad, p.ldd, hi, lo, count, list);
     if (launch_status() != HSCALE_OK) return HSCALE_ERR_HIP;
-    const LfTile tile = gram ? kLfWide : p.tile;
+    const LfTile tile = gram || !small_tiles ? kLfWide : p.tile;
     const int64_t tile_tokens = kLfTiles[tile].tokens;
-    int64_t pass_tiles = (int64_t)((direct_bytes - p.partial_offset) / ((size_t)out * sizeof(double)));
-    if (pass_tiles > p.tiles_per_pass) pass_tiles = p.tiles_per_pass;
-    const int64_t pass_tokens = pass_tiles * tile_tokens;
+    const int64_t pass_tokens = (tile == kLfWide ? p.wide_per_pass : p.tiles_per_pass) * tile_tokens;
     for (int64_t t0 = 0; t0 < tokens; t0 += pass_tokens) {
         LfArgs a;
         a.tokens = tokens - t0 < pass_tokens ? tokens - t0 : pass_tokens;
@@ -1073,7 +1072,7 @@ int hscale_output_error(const void *X, int64_t tokens, int64_t in, const void *W
         a.lo = lo;
         a.ldd = p.ldd;
         a.out = out;
-        a.ntiles = gram ? p.ntiles : p.row_tiles;
+        a.ntiles = tile == kLfWide ? p.ntiles : p.row_tiles;
         a.partial = partial;
         a.count = count;
         const int64_t tiles = (a.tokens + tile_tokens - 1) / tile_tokens;

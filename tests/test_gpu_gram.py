@@ -205,11 +205,27 @@ def test_direct_tiles_and_smaller_workspaces(hs, T, n, m):
     ref = _reference(X, W, s_g, codes, packed)
     full = hs.output_error(X, W, s_g, codes, packed)
     least = torch.empty(_direct_bytes(T, n, m), dtype=torch.uint8, device=DEV)
-    passes = hs.output_error(X, W, s_g, codes, packed, workspace=least)  # small tiles in several passes
+    passes = hs.output_error(X, W, s_g, codes, packed, workspace=least)  # 384 x 256 tiles
     torch.cuda.synchronize()
     print(f"[direct {T}x{n}x{m}] max rel {_rel(full, ref):.2e}", flush=True)
     assert _rel(full, ref) <= REL_TOL
     assert ((full - passes).abs() <= 1e-12 * full).all()
+
+
+@pytest.mark.parametrize("T,n,m", [(385, 1040, 513), (3000, 96, 700), (2049, 528, 4100), (5000, 80, 4096)])
+def test_a_smaller_workspace_takes_one_pass(hs, T, n, m):
+    """The least workspace holds the partials of all tokens in 384-token
+    tiles: one pass leaves them there, and they add up to the result.  Small
+    tiles in it would take several passes over the same partials."""
+    X, W = _case(T, n, m, seed=T + m)
+    s_g, codes, packed = _stored(hs, W)
+    tiles = -(-T // 384)
+    ws = torch.zeros(_direct_bytes(T, n, m), dtype=torch.uint8, device=DEV)
+    L = hs.output_error(X, W, s_g, codes, packed, workspace=ws)
+    parts = ws[ws.numel() - tiles * m * 8:].view(torch.float64).view(tiles, m)
+    torch.cuda.synchronize()
+    print(f"[least {T}x{n}x{m}]", flush=True)
+    assert ((parts.sum(0) - L).abs() <= 1e-13 * L).all()
 
 
 def test_very_many_rows(hs):
