@@ -347,9 +347,15 @@ int hscale_shift_summary(const int8_t *shift, const float *err_best,
                          double *sum_best, double *sum_rel, void *workspace,
                          size_t workspace_bytes, hipStream_t stream);
 
-/* Workspace bytes hscale_output_error needs (0 when any size is 0). */
+/* Workspace bytes with which hscale_output_error is fastest (0 when any size
+ * is 0). */
 size_t hscale_output_error_workspace_bytes(int64_t tokens, int64_t in,
                                            int64_t out);
+
+/* The smallest workspace it accepts: enough for the direct product alone, for
+ * callers that are short of memory (0 when any size is 0). */
+size_t hscale_output_error_least_workspace_bytes(int64_t tokens, int64_t in,
+                                                 int64_t out);
 
 /*
  * Layer-output error of a stored NVFP4 tensor on calibration activations
@@ -390,11 +396,13 @@ size_t hscale_output_error_workspace_bytes(int64_t tokens, int64_t in,
  * packed_e2m1  uint8 [out, in / 2], 8-byte aligned, element 2k in the low
  *              nibble of byte k
  * row_err      fp64 [out], 8-byte aligned, in/out
- * workspace    >= hscale_output_error_workspace_bytes(tokens, in, out)
- *              bytes, 256-byte aligned, scratch owned by the caller (it holds
- *              the two dW planes and per-tile partial sums, and for G its
- *              partial tiles and two planes: at most 1.2 GB beside the
- *              planes); one that holds only the direct product's is enough
+ * workspace    256-byte aligned scratch owned by the caller, of
+ *              hscale_output_error_workspace_bytes(tokens, in, out) bytes: the
+ *              two dW planes and per-tile partial sums, and for G (in <=
+ *              16384) its partial tiles, at most 1.2 GB, their fp64 sums where
+ *              they need several passes, at most 1.1 GB, and G's two planes,
+ *              at most 1.1 GB.  One of hscale_output_error_least_workspace_
+ *              bytes is enough: all rows then take the direct product
  * in % 16 == 0 and in <= 2^21 (HSCALE_ERR_SHAPE beyond: the kernel
  * addresses a tile of X and of dW with 32-bit offsets); global_scale as
  * hscale_search.  tokens, in or out = 0 adds nothing.

@@ -35,6 +35,7 @@ EXPORTS = (
     "hscale_shift_summary_workspace_bytes",
     "hscale_shift_summary",
     "hscale_output_error_workspace_bytes",
+    "hscale_output_error_least_workspace_bytes",
     "hscale_output_error",
     "hscale_quantize",
 )
@@ -101,6 +102,8 @@ def load() -> ctypes.CDLL:
     lib.hscale_shift_summary.restype = ctypes.c_int
     lib.hscale_output_error_workspace_bytes.argtypes = [i64, i64, i64]
     lib.hscale_output_error_workspace_bytes.restype = sz
+    lib.hscale_output_error_least_workspace_bytes.argtypes = [i64, i64, i64]
+    lib.hscale_output_error_least_workspace_bytes.restype = sz
     lib.hscale_output_error.argtypes = [P, i64, i64, P, i64, f32, P, P, P, P, sz, P]
     lib.hscale_output_error.restype = ctypes.c_int
     _lib = lib
@@ -205,6 +208,10 @@ def hscale_shift_summary(shift: int, err_best: int, err_init: int, groups: int, 
 
 def hscale_output_error_workspace_bytes(tokens: int, in_: int, out: int) -> int:
     return load().hscale_output_error_workspace_bytes(tokens, in_, out)
+
+
+def hscale_output_error_least_workspace_bytes(tokens: int, in_: int, out: int) -> int:
+    return load().hscale_output_error_least_workspace_bytes(tokens, in_, out)
 
 
 def hscale_output_error(X: int, tokens: int, in_: int, W: int, out: int, global_scale: float, scale_codes: int,

@@ -998,6 +998,11 @@ int hscale_shift_summary(const int8_t *shift, const float *err_best, const float
     return launch_status();
 }
 
+size_t hscale_output_error_least_workspace_bytes(int64_t tokens, int64_t in, int64_t out) {
+    if (in % kGroup != 0 || in > kLfMaxIn || (in > 0 && out > kMaxGroups / (in / kGroup))) return 0;
+    return lfull_plan(tokens, in, out).least;
+}
+
 size_t hscale_output_error_workspace_bytes(int64_t tokens, int64_t in, int64_t out) {
     if (in % kGroup != 0 || in > kLfMaxIn || (in > 0 && out > kMaxGroups / (in / kGroup))) return 0;
     const LfPlan p = lfull_plan(tokens, in, out);

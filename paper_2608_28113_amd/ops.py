@@ -348,7 +348,7 @@ def shift_summary(shift: torch.Tensor, err_best: torch.Tensor, err_init: torch.T
 
 
 def output_error_workspace_bytes(tokens: int, in_features: int, out_features: int) -> int:
-    """Bytes of scratch output_error needs."""
+    """Bytes of scratch with which output_error is fastest."""
     return _lib.hscale_output_error_workspace_bytes(tokens, in_features, out_features)
 
 
@@ -358,7 +358,8 @@ def output_error(X: torch.Tensor, W: torch.Tensor, global_scale: float, scale_co
     """Eq. 3 per output row: row_err[r] += sum_t (X dW^T)_tr^2 with dW = W - W^
     the rounding error of the stored NVFP4 tensor (scale_codes, packed_e2m1).
     row_err is fp64 [out] (zeros when not given); the layer's L_full is its
-    sum."""
+    sum.  Without a workspace it allocates one of output_error_workspace_bytes,
+    or the least one that the library accepts where that much is not free."""
     _bf16_matrix(X, "X")
     _bf16_matrix(W, "W")
     T, n = X.shape
@@ -371,7 +372,14 @@ def output_error(X: torch.Tensor, W: torch.Tensor, global_scale: float, scale_co
     if row_err is None:
         row_err = torch.zeros(m, dtype=torch.float64, device=dev)
     _tensor(row_err, "row_err", torch.float64, (m,), dev)
-    ws_ptr, ws_bytes = _workspace(workspace, output_error_workspace_bytes(T, n, m), dev)
+    need = output_error_workspace_bytes(T, n, m)
+    try:
+        ws_ptr, ws_bytes = _workspace(workspace, need, dev)
+    except torch.OutOfMemoryError:
+        least = _lib.hscale_output_error_least_workspace_bytes(T, n, m)
+        if least == need:
+            raise
+        ws_ptr, ws_bytes = _workspace(None, least, dev)
     _check(_call(dev, _lib.hscale_output_error, X.data_ptr(), T, n, W.data_ptr(), m, float(global_scale),
                  scale_codes.data_ptr(), packed_e2m1.data_ptr(), row_err.data_ptr(), ws_ptr, ws_bytes,
                  _stream(stream, dev)), "hscale_output_error")

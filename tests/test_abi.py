@@ -129,8 +129,28 @@ def test_output_error_of_very_many_rows_goes_direct(L):
     for m in (1 << 26, 1 << 27):
         direct = 2 * m * 32 * 2 + -(-T // 384) * m * 8
         assert L.hscale_output_error_workspace_bytes(T, n, m) == direct, m
+        assert L.hscale_output_error_least_workspace_bytes(T, n, m) == direct, m
     m = 1 << 25
     assert L.hscale_output_error_workspace_bytes(T, n, m) > 2 * m * 32 * 2 + -(-T // 384) * m * 8
+
+
+def test_output_error_workspace_sizes(L):
+    """The least workspace is that of two padded bf16 planes and at most 1024
+    partials of 384 tokens; the one asked for holds it, and what the faster
+    route adds stays within what the header says of it."""
+    for n in (16, 240, 1024, 4096, 14336, 16384, 16400, 28672):
+        for m in (1, 255, 1024, 4096, 14336, 28672):
+            for T in (1, 100, 2048, 16384, 65537, 262144):
+                ldd, rows = -(-n // 32) * 32, -(-m // 256) * 256
+                direct = 2 * (-(-rows * ldd * 2 // 256) * 256) + min(-(-T // 384), 1024) * m * 8
+                least, asked = (f(T, n, m) for f in (L.hscale_output_error_least_workspace_bytes,
+                                                     L.hscale_output_error_workspace_bytes))
+                assert least == direct and asked >= least, (T, n, m)
+                small_tiles = min(-(-T // 64), 1024) * m * 8
+                route = (4608 << 18) + (2080 << 19) + 2 * 16384 ** 2 * 2 + (64 + 4) * 8 * m + (1 << 20)
+                assert asked <= least + small_tiles + route, (T, n, m)
+    assert L.hscale_output_error_least_workspace_bytes(0, 16, 16) == 0
+    assert L.hscale_output_error_least_workspace_bytes(16, 17, 16) == 0
 
 
 def test_search_validation(L):

@@ -228,6 +228,29 @@ def test_a_smaller_workspace_takes_one_pass(hs, T, n, m):
     assert ((parts.sum(0) - L).abs() <= 1e-13 * L).all()
 
 
+def test_short_of_memory_takes_the_least_workspace(hs):
+    """Where the faster route's workspace does not fit in the memory left, the
+    call still runs in the direct product's, with its result."""
+    T, n, m = 120000, 1040, 4100
+    X, W = _case(T, n, m, seed=2)
+    s_g, codes, packed = _stored(hs, W)
+    need, least = hs.output_error_workspace_bytes(T, n, m), _direct_bytes(T, n, m)
+    plain = hs.output_error(X, W, s_g, codes, packed, workspace=torch.empty(least, dtype=torch.uint8, device=DEV))
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    room = least + (32 << 20)
+    assert need > room
+    total = torch.cuda.get_device_properties(DEV).total_memory
+    print(f"[short of memory {T}x{n}x{m}] asked for {need}, room for {room}", flush=True)
+    torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + room) / total)
+    try:
+        L = hs.output_error(X, W, s_g, codes, packed)
+        torch.cuda.synchronize()
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert torch.equal(L, plain)
+
+
 def test_very_many_rows(hs):
     """2^26 rows, more than one launch of the other route's row kernel holds."""
     T, n, m = 8000, 16, 1 << 26
