@@ -419,14 +419,18 @@ __device__ __forceinline__ u32x4 raw_descriptor(const void *p, uint32_t bytes) {
 // Starts a copy of 16 bytes per lane from the buffer to LDS at `dst` + 16 x
 // lane; the caller waits for vmcnt.  In assembly because the compiler, which
 // cannot tell the buffer being filled from the one being read, puts a wait
-// for the builtin's copies before LDS reads.  It writes no register but M0,
-// which nothing else in these kernels uses.
+// for the builtin's copies before LDS reads.  M0 holds the LDS address and is
+// declared as written, so the compiler keeps nothing of its own in it across
+// (it warns that the register is one it reserves, which is what is declared).
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void load_to_lds(u32x4 rsrc, uint32_t offset, uint32_t dst) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                  :
                  : "s"(dst), "v"(offset), "s"(rsrc)
-                 : "memory");
+                 : "m0", "memory");
 }
+#pragma clang diagnostic pop
 
 constexpr int kWaitAll = 0x70;  // s_waitcnt vmcnt(0) lgkmcnt(0)
 constexpr int kSchedMfma = 0x008, kSchedLdsRead = 0x100;  // instruction classes of the scheduling groups
