@@ -90,6 +90,37 @@ def compare_search(W_bits: np.ndarray, h32: np.ndarray, s_g: float, down: int, u
     )
 
 
+# A search of at most this many groups may take the kernel that splits a group
+# over four lanes; larger ones take one lane per group.
+SPLIT_GROUPS = 65536
+
+
+def assert_same_in_a_large_launch(hs, W, h, s_g, down, up, codes, packed, init="maxabs", stats=None):
+    """The rows of W repeated until the launch has one lane per group give
+    codes and packed (and the statistics of the search_stats result `stats`)
+    of the small launch, row for row.  The small result is the one compared
+    with the oracle, so the residue-class walk, the plain walk of long windows
+    and the fall-back between them are held to it as well."""
+    import torch
+
+    m, G = codes.shape
+    if m * G > SPLIT_GROUPS:
+        return 1
+    reps = 1 + SPLIT_GROUPS // (m * G)
+    init = init.repeat(reps, 1) if isinstance(init, torch.Tensor) else init
+    W = W.repeat(reps, 1)
+    if stats is None:
+        c, p = hs.search(W, h, s_g, down=down, up=up, init=init)
+    else:
+        st = hs.search_stats(W, h, s_g, down, up, init=init)
+        c, p = st["scale_codes"], st["packed_e2m1"]
+        for key in ("shift", "err_best", "err_init"):
+            want = stats[key]
+            assert torch.equal(st[key], want.repeat(reps, 1)), (key, reps)
+    assert torch.equal(c, codes.repeat(reps, 1)) and torch.equal(p, packed.repeat(reps, 1)), reps
+    return reps
+
+
 # fp32 score of one group against the fp64 oracle: each of the 16 positive
 # terms carries a few roundings (residual, square, weight) and the sum runs
 # 4 chains of 4 then a 2-level tree, about 10 units of 2^-24 in all; the

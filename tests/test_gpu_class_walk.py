@@ -10,6 +10,10 @@ weights on exact E2M1 midpoints of such member candidates (a power-of-two
 global scale makes S[c] short), count in numpy how many midpoints reach the
 scale-2 and scale-4 conversions, and compare every group with the oracle
 through the plain search, the statistics search and the batched search.
+
+A launch this small splits each group over lanes, except in the batched
+search; the plain and the statistics search therefore also run on the same
+rows repeated to a launch that walks the classes, and must give the same.
 """
 from __future__ import annotations
 
@@ -101,7 +105,7 @@ def test_class_walk_exact_midpoints(hs, down, up):
     class_walk, counts = _member_midpoints(Wb, down, up)
     print(f"[class walk midpoints] down={down} up={up} class_walk={class_walk} "
           f"scale2_midpoints={counts[2]} scale4_midpoints={counts[4]}", flush=True)
-    assert class_walk, "every wave must take the residue-class walk"
+    assert class_walk, "every wave must take the residue-class walk where a lane has a group"
     assert counts[2] > 500
     if up - (-down) >= 16:  # some class has a third member
         assert counts[4] > 50
@@ -115,7 +119,9 @@ def test_class_walk_exact_midpoints(hs, down, up):
     assert rep["ok"], {k: v for k, v in rep.items() if k not in ("oracle", "tie_mask", "init_tie_mask",
                                                                  "err_at_gpu_codes")}
 
+    assert parity.assert_same_in_a_large_launch(hs, W, h, S_G, down, up, codes, packed) > 1
     st = hs.search_stats(W, h, S_G, down, up)
+    parity.assert_same_in_a_large_launch(hs, W, h, S_G, down, up, codes, packed, stats=st)
     srep = parity.compare_stats(Wb, h32, S_G, down, up, {k: v.cpu().numpy() for k, v in st.items()})
     print(f"[class walk midpoints] stats shift_mismatches={srep['shift_mismatches']} "
           f"err_best_max_rel={srep['err_best_max_rel']:.2e}", flush=True)
@@ -147,12 +153,15 @@ def test_class_walk_overflowing_scores_keep_a_real_candidate(hs):
     for down, up in ((0, 15), (9, 6), (8, 8)):
         waves = c0.reshape(-1, 64)
         assert np.all(waves - down >= 8) and np.all(waves + up <= 126)  # class walk in every wave
-        codes, packed = hs.search(W.to(DEV), torch.from_numpy(h32).to(DEV), s_g, down=down, up=up)
+        Wd, hd = W.to(DEV), torch.from_numpy(h32).to(DEV)
+        codes, packed = hs.search(Wd, hd, s_g, down=down, up=up)
+        st = hs.search_stats(Wd, hd, s_g, down, up)
+        assert parity.assert_same_in_a_large_launch(hs, Wd, hd, s_g, down, up, codes, packed) > 1
+        parity.assert_same_in_a_large_launch(hs, Wd, hd, s_g, down, up, codes, packed, stats=st)
         codes = codes.cpu().numpy()
         want = np.clip(c0 - down, 1, 126).astype(np.uint8)
         assert np.array_equal(codes, want), (down, up)
         at, _ = oracle.quantize(Wb, s_g, codes)
         assert np.array_equal(packed.cpu().numpy(), at), (down, up)
-        st = hs.search_stats(W.to(DEV), torch.from_numpy(h32).to(DEV), s_g, down, up)
         assert torch.all(st["shift"] == -down)
         assert torch.all(torch.isinf(st["err_best"]))

@@ -35,6 +35,7 @@ def _bits_to_bf16(bits: np.ndarray, device=DEV) -> torch.Tensor:
 
 def _run_search(hs, W, h, s_g, down, up):
     codes, packed = hs.search(W, h, s_g, down=down, up=up)
+    parity.assert_same_in_a_large_launch(hs, W, h, s_g, down, up, codes, packed)
     torch.cuda.synchronize()
     return codes.cpu().numpy(), packed.cpu().numpy()
 
@@ -365,8 +366,9 @@ def test_block_layers_small_windows(hs):
 def test_search_class_walk_paths(hs, down, up):
     """Windows of 16..24 candidates walk the residue classes c mod 8 when
     every lane of a wave has only normal, unclipped candidates; a wave with
-    one lane near either end of the ladder takes the plain walk.  Both must
-    equal the oracle."""
+    one lane near either end of the ladder takes the plain walk.  So do they
+    in the large launch of the same rows; the small one splits its groups over
+    lanes.  All must equal the oracle."""
     rng = np.random.default_rng(down * 31 + up)
     m, n = 64, 1024  # 64 groups per row: one wave per row
     w = (rng.standard_normal((m, n)) * 0.02).astype(np.float32)

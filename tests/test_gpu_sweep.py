@@ -3,7 +3,9 @@
 
 Each case draws its own shape (1-69 rows, 1-89 groups per row: ragged
 against the 64-lane wave and the 256-lane block), window (0-24 shifts each
-way, so both the plain walk and the residue-class walk run), initial-code
+way: the small launch splits a group over lanes from 8 candidates on, and the
+same rows repeated to a large launch take the plain walk or the residue-class
+walk, with the same result), initial-code
 rule (max-abs, 4over6, or given code bytes over the whole byte range, which
 the search clips), global scale (the harness rule, a power of two that puts
 weights on exact E2M1 midpoints, one large enough that codes clamp to 1, one
@@ -82,6 +84,8 @@ def test_search_sweep_matches_oracle(hs, i):
         print(f"[sweep {i}] stats: near_ties={srep['near_ties']} mismatches={srep['mismatches']} "
               f"shift_mismatches={rep['shift_mismatches']} err_best_rel={rep['err_best_max_rel']:.2e}", flush=True)
         assert rep["ok"], {k: v for k, v in rep.items() if k != "search"}
+        parity.assert_same_in_a_large_launch(hs, Wd, hd, s_g, down, up, out["scale_codes"], out["packed_e2m1"],
+                                             init=init_gpu, stats=out)
     else:
         codes, packed = hs.search(Wd, hd, s_g, down=down, up=up, init=init_gpu)
         torch.cuda.synchronize()
@@ -91,3 +95,4 @@ def test_search_sweep_matches_oracle(hs, i):
               f"mismatches={rep['mismatches']} invalid={rep['invalid']}", flush=True)
         assert rep["ok"], {k: v for k, v in rep.items() if k not in ("oracle", "tie_mask", "init_tie_mask",
                                                                       "err_at_gpu_codes")}
+        parity.assert_same_in_a_large_launch(hs, Wd, hd, s_g, down, up, codes, packed, init=init_gpu)

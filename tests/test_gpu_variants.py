@@ -47,6 +47,7 @@ def test_4over6_tiny_parity(hs, tiny, down, up):
     W, h, s_g = tiny
     codes, packed = hs.search(W, h, s_g, down=down, up=up, init="4over6")
     _check(W, h, s_g, down, up, codes, packed, "4over6", "4over6 tiny")
+    parity.assert_same_in_a_large_launch(hs, W, h, s_g, down, up, codes, packed, init="4over6")
 
 
 def test_4over6_window0_is_the_4over6_quantizer(hs, tiny):
@@ -82,6 +83,7 @@ def test_search_from_given_codes(hs, tiny, down, up):
     init_t = torch.from_numpy(init).to(DEV)
     codes, packed = hs.search(W, h, s_g, down=down, up=up, init=init_t)
     _check(W, h, s_g, down, up, codes, packed, init, "given init")
+    parity.assert_same_in_a_large_launch(hs, W, h, s_g, down, up, codes, packed, init=init_t)
 
 
 def test_search_from_in_place_and_equivalence(hs, tiny):
@@ -98,30 +100,62 @@ def test_search_from_in_place_and_equivalence(hs, tiny):
     assert torch.equal(buf, c_ref)
 
 
-def test_search_block_strided(hs):
+@pytest.mark.parametrize("down,up", [(4, 4), (9, 6), (13, 12)])
+@pytest.mark.parametrize("init", ["maxabs", "4over6", "given"])
+def test_search_block_strided(hs, init, down, up):
     """A column block of a wider matrix with padded rows: only the block's
-    codes and bytes are written, and they equal the oracle's on the block."""
+    codes and bytes are written, and they equal the oracle's on the block.  96
+    rows are 2304 groups, split over lanes; 30 times as many take one lane per
+    group (the plain walk, the class walk, and a window too long for it)."""
     wl = CONFIGS["tiny"]
     m, N, pad = 96, 1024, 64
     a, b = 256, 640
     full = make_weight(wl, "cpu", shape=(m, N + pad)).to(DEV)
-    Wfull = full[:, :N]  # row stride N + pad
-    h = torch.exp(torch.randn(N, device=DEV))
-    s_g = harness_global_scale(Wfull)
-    codes = torch.full((m, N // 16 + 3), 0xAB, dtype=torch.uint8, device=DEV)
-    packed = torch.full((m, N // 2 + 8), 0xCD, dtype=torch.uint8, device=DEV)
-    cv = codes[:, a // 16:b // 16]
-    pv = packed[:, a // 2:b // 2]
-    hs.search_block(Wfull[:, a:b], h[a:b].contiguous(), s_g, 4, 4, cv, pv)
-    torch.cuda.synchronize()
-    c = codes.cpu().numpy()
-    p = packed.cpu().numpy()
-    assert np.all(c[:, :a // 16] == 0xAB) and np.all(c[:, b // 16:] == 0xAB)
-    assert np.all(p[:, :a // 2] == 0xCD) and np.all(p[:, b // 2:] == 0xCD)
-    Wb = tensor_bits(Wfull[:, a:b].contiguous())
-    rep = parity.compare_search(Wb, h[a:b].cpu().numpy(), s_g, 4, 4, c[:, a // 16:b // 16],
-                                p[:, a // 2:b // 2])
-    assert rep["ok"], {k: v for k, v in rep.items() if k != "oracle"}
+    h = torch.exp(torch.randn(N, generator=torch.Generator().manual_seed(4))).to(DEV)
+    s_g = harness_global_scale(full[:, :N])
+    Wb = tensor_bits(full[:, a:b].contiguous())
+    given = oracle.anchor_codes(Wb, s_g, 6.0).astype(np.int64) + np.random.default_rng(5).integers(-6, 7, (m, 24))
+    given = np.clip(given, 0, 255).astype(np.uint8)
+    for reps in (1, 30):
+        Wfull = full.repeat(reps, 1)[:, :N]  # row stride N + pad
+        codes = torch.full((reps * m, N // 16 + 3), 0xAB, dtype=torch.uint8, device=DEV)
+        packed = torch.full((reps * m, N // 2 + 8), 0xCD, dtype=torch.uint8, device=DEV)
+        init_t = init
+        if init == "given":
+            init_t = torch.zeros((reps * m, 24 + 7), dtype=torch.uint8, device=DEV)[:, 3:27]
+            init_t.copy_(torch.from_numpy(given).to(DEV).repeat(reps, 1))
+        hs.search_block(Wfull[:, a:b], h[a:b].contiguous(), s_g, down, up, codes[:, a // 16:b // 16],
+                        packed[:, a // 2:b // 2], init=init_t)
+        torch.cuda.synchronize()
+        c = codes.cpu().numpy()
+        p = packed.cpu().numpy()
+        assert np.all(c[:, :a // 16] == 0xAB) and np.all(c[:, b // 16:] == 0xAB)
+        assert np.all(p[:, :a // 2] == 0xCD) and np.all(p[:, b // 2:] == 0xCD)
+        c, p = c[:, a // 16:b // 16], p[:, a // 2:b // 2]
+        if reps == 1:
+            rep = parity.compare_search(Wb, h[a:b].cpu().numpy(), s_g, down, up, c, p,
+                                        init={"maxabs": "rtn", "4over6": "4over6"}.get(init, given))
+            assert rep["ok"], {k: v for k, v in rep.items() if k != "oracle"}
+            small = c, p
+        else:
+            assert np.array_equal(c, np.tile(small[0], (reps, 1))) and np.array_equal(p, np.tile(small[1], (reps, 1)))
+
+
+# Both sides of every line of the rule that splits a group over four lanes:
+# 32768 and 65536 groups, 8 and 16 candidates.
+@pytest.mark.parametrize("groups", [32768, 32769, 65536, 65537])
+@pytest.mark.parametrize("down,up", [(3, 3), (3, 4), (7, 7), (8, 7)])
+def test_split_search_lines(hs, groups, down, up):
+    wl = CONFIGS["tiny"]
+    W = make_weight(wl, "cpu", shape=(groups, 16)).to(DEV)
+    h = torch.exp(torch.randn(16, generator=torch.Generator().manual_seed(6))).to(DEV)
+    s_g = harness_global_scale(W)
+    codes, packed = hs.search(W, h, s_g, down=down, up=up)
+    _check(W, h, s_g, down, up, codes, packed, "rtn", f"split lines {groups}")
+    st = hs.search_stats(W, h, s_g, down, up)
+    assert torch.equal(st["scale_codes"], codes) and torch.equal(st["packed_e2m1"], packed)
+    rep = parity.compare_stats(tensor_bits(W), h.cpu().numpy(), s_g, down, up, {k: v.cpu().numpy() for k, v in st.items()})
+    assert rep["ok"], {k: v for k, v in rep.items() if k != "search"}
 
 
 @pytest.mark.parametrize("init", ["maxabs", "4over6"])
