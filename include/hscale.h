@@ -377,8 +377,8 @@ size_t hscale_output_error_least_workspace_bytes(int64_t tokens, int64_t in,
  * and sums are fp64 in a fixed order.  Where many output rows share a long X
  * (a rule on the sizes) and the workspace holds what
  * hscale_output_error_workspace_bytes says, the same sums come from
- * G = X^T X instead: exact bf16 products accumulated in fp32 over token
- * chunks, added in fp64; G's diagonal applied in fp64, the rest as 22-bit
+ * G = X^T X instead: exact bf16 products accumulated in fp32 over at most
+ * 2048 tokens, those sums in fp32 over at most 16 passes, the rest in fp64; G's diagonal applied in fp64, the rest as 22-bit
  * scaled values; rows whose terms cancel to below 1/4 of their diagonal
  * part, or leave fp32's range, are computed by the direct product.  Both are
  * bitwise reproducible for a given problem and workspace size; the second is
@@ -400,8 +400,8 @@ size_t hscale_output_error_least_workspace_bytes(int64_t tokens, int64_t in,
  *              hscale_output_error_workspace_bytes(tokens, in, out) bytes: the
  *              two dW planes and per-tile partial sums, and for G (in <=
  *              16384) its partial tiles, at most 1.2 GB, their fp64 sums where
- *              they need several passes, at most 1.1 GB, and G's two planes,
- *              at most 1.1 GB.  One of hscale_output_error_least_workspace_
+ *              they need more than 16 passes, at most 1.1 GB, and G's two
+ *              planes, at most 1.1 GB.  One of hscale_output_error_least_workspace_
  *              bytes is enough: all rows then take the direct product
  * in % 16 == 0 and in <= 2^21 (HSCALE_ERR_SHAPE beyond: the kernel
  * addresses a tile of X and of dW with 32-bit offsets); global_scale as

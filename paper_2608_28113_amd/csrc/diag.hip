@@ -890,25 +890,30 @@ int gram_run(const GramPlan &gp, const LfPlan &p, const u32x4 *X, int64_t tokens
     uint32_t *count = reinterpret_cast<uint32_t *>(ws + gp.list_offset);
     u32x4 *hi = reinterpret_cast<u32x4 *>(ws), *lo = reinterpret_cast<u32x4 *>(ws + p.plane_bytes);
     const int least = gram_least_exponent(tokens);
-    for (int64_t c0 = 0; c0 < gp.chunks; c0 += gp.pass_chunks) {
-        const int64_t chunks = gp.chunks - c0 < gp.pass_chunks ? gp.chunks - c0 : gp.pass_chunks;
-        const int64_t t0 = c0 * gp.chunk;
+    const int64_t passes = (gp.chunks + gp.pass_chunks - 1) / gp.pass_chunks;
+    for (int64_t k = 0; k < passes; ++k) {
+        const int64_t t0 = k * gp.pass_chunks * gp.chunk;
+        const int64_t chunks = k + 1 < passes ? gp.pass_chunks : gp.chunks - k * gp.pass_chunks;
         GramArgs a;
         a.X = X + t0 * (in / 8);
         a.tokens = tokens - t0 < chunks * gp.chunk ? tokens - t0 : chunks * gp.chunk;
         a.in = in;
         a.chunk = gp.chunk;
         a.tri = (int)gp.tri;
+        a.add = k % kGrCarry != 0;
         a.partial = partial;
         hipLaunchKernelGGL(gram_kernel, dim3((unsigned)(chunks * gp.tri)), dim3(kGrThreads), 0, stream, a);
         if (launch_status() != HSCALE_OK) return HSCALE_ERR_HIP;
-        hipLaunchKernelGGL(gram_diag, dim3((unsigned)gp.nt), dim3(kGrTile), 0, stream, partial, (int)gp.tri,
-                           (int)chunks, c0 == 0, least, diag, scale);
+        const bool last = k + 1 == passes, first = k < kGrCarry;
+        if (!last && (k + 1) % kGrCarry != 0) continue;
+        const int sums = (int)(a.add ? gp.pass_chunks : chunks);  // partials that hold something
+        hipLaunchKernelGGL(gram_diag, dim3((unsigned)gp.nt), dim3(kGrTile), 0, stream, partial, (int)gp.tri, sums,
+                           first, least, diag, scale);
         if (launch_status() != HSCALE_OK) return HSCALE_ERR_HIP;
         hipLaunchKernelGGL(gram_reduce, dim3((unsigned)(gp.tri * (kGrUnitVecs / 256))), dim3(256), 0, stream, partial,
-                           (int)gp.tri, (int)chunks, c0 == 0, c0 + chunks == gp.chunks,
-                           reinterpret_cast<double4 *>(ws + gp.g64_offset), gp.ldg, diag, least,
-                           reinterpret_cast<uint2 *>(planes), reinterpret_cast<uint2 *>(planes + gp.plane_bytes));
+                           (int)gp.tri, sums, first, last, reinterpret_cast<double4 *>(ws + gp.g64_offset), gp.ldg,
+                           diag, least, reinterpret_cast<uint2 *>(planes),
+                           reinterpret_cast<uint2 *>(planes + gp.plane_bytes));
         if (launch_status() != HSCALE_OK) return HSCALE_ERR_HIP;
     }
     hipLaunchKernelGGL(gram_rows, dim3((unsigned)((out + kGrRowBlock - 1) / kGrRowBlock)), dim3(kGrRowThreads), 0,

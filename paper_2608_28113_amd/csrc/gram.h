@@ -7,11 +7,11 @@
 // the direct product, whose dW needs two bf16 parts.
 //
 //   gram_kernel   fp32 partials of the lower-triangle tiles of G over token
-//                 chunks, on the matrix cores
+//                 chunks, on the matrix cores, in passes that add to them
 //   gram_diag     the diagonal of G in fp64, which also scales the rest: the
 //                 power of two 2^k_j next above sqrt(G_jj), or above what fp32
 //                 squares can hide of it
-//   gram_reduce   fp64 sum of the chunks; the off-diagonal G_ij / 2^(k_i + k_j)
+//   gram_reduce   fp64 sum of the partials; the off-diagonal G_ij / 2^(k_i + k_j)
 //                 (times two outside the diagonal tiles) as two f16 planes,
 //                 22 bits
 //   gram_rows     per row: the diagonal part D = sum_j G_jj dW_rj^2 in fp64,
@@ -48,12 +48,17 @@ constexpr int kGrUnitVecs = kGrTile * kGrTile / 4;   // float4 of a tile's parti
 // row's sum up to 2.1e-4 in chains of 17500 tokens, 1.8e-5 of 4096, 3.2e-6 of
 // 2048 (direct: 1.2e-5); two tokens in turn, on average 3.4e-5, 8.4e-6 and
 // 3.3e-6 (direct: 4.6e-6).  The partials of short chains cost traffic: with
-// 14336 rows 4.6 ms, 5.1, 5.8, and 7.6 with chains of 1024.  Adding each
+// 14336 rows 4.6 ms, 5.1, 5.6, and 7.6 with chains of 1024.  Adding each
 // accumulator to the block's partial every 2048 tokens instead of ending the
 // chunk took 6.0 ms.
 constexpr int kGrChunkTokens = 2048;
 constexpr int kGrMinChunk = 1024;
 constexpr int64_t kGrMaxUnits = 4608;  // partial tiles per pass (1.2 GB of workspace)
+// Passes whose partials add up in fp32 before they go to fp64: 15 roundings
+// beside the 128 of a chain.  Sums that go to fp64 and back in every pass cost
+// 16 bytes of traffic an entry more, which tells where two chunks fill a pass
+// (65536 x 16384 columns and rows, 16 passes: 31.0 ms, and about 36).
+constexpr int64_t kGrCarry = 16;
 constexpr int64_t kGrMaxTiles = 64;    // in <= 16384
 constexpr int64_t kGrMaxOut = (int64_t)1 << 25;  // gram_rows' grid: 64 threads a row, below 2^32 in all
 constexpr uint32_t kGrOutside = 0x7FFF0000u;  // beyond every descriptor's range
@@ -63,6 +68,7 @@ struct GramArgs {
     int64_t tokens, in;
     int64_t chunk;   // tokens per unit, a multiple of kGrBK
     int tri;         // tiles of the lower triangle
+    bool add;        // to the partials of the passes before
     float4 *partial; // [units][kGrUnitVecs]
 };
 
@@ -199,11 +205,17 @@ __global__ __launch_bounds__(kGrThreads, 2) void gram_kernel(const GramArgs a) {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < 2; ++j) {
+            float4 v[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                dst[((i * 2 + j) * 4 + e) * 64] = make_float4(acc[i][j][4 * e], acc[i][j][4 * e + 1],
-                                                              acc[i][j][4 * e + 2], acc[i][j][4 * e + 3]);
+                v[e] = a.add ? dst[((i * 2 + j) * 4 + e) * 64] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                dst[((i * 2 + j) * 4 + e) * 64] =
+                    make_float4(v[e].x + acc[i][j][4 * e], v[e].y + acc[i][j][4 * e + 1],
+                                v[e].z + acc[i][j][4 * e + 2], v[e].w + acc[i][j][4 * e + 3]);
+        }
 }
 
 // Float4 (and component) of a tile's partial that holds row `row`, column
@@ -234,8 +246,8 @@ inline int gram_least_exponent(int64_t tokens) {
     return k;
 }
 
-// Diagonal of column tile blockIdx.x: the chunks' partials in chunk order, on
-// top of the earlier passes' sums, and the channels' 2^k.
+// Diagonal of column tile blockIdx.x: the partials in chunk order, on top of
+// the sums so far, and the channels' 2^k.
 __global__ __launch_bounds__(kGrTile) void gram_diag(const float4 *__restrict__ partial, int tri, int chunks,
                                                      bool first, int least, double *__restrict__ diag,
                                                      float *__restrict__ scale) {
@@ -262,9 +274,9 @@ __device__ __forceinline__ void split_f16(float f, uint32_t &hi, uint32_t &lo) {
 // below 2^-34 of sqrt(G_ii G_jj).
 constexpr int kGrPlaneExp = 10;
 
-// One thread per float4 of a tile: the fp64 sum of the chunks' partials in
-// chunk order, on top of the earlier passes' sums (kept in g64; not read
-// when `first`, not written when `last`).  The last pass writes the planes.
+// One thread per float4 of a tile: the fp64 sum of the partials in chunk
+// order, on top of the sums so far (kept in g64; not read when `first`, not
+// written when `last`).  The last one writes the planes.
 __global__ __launch_bounds__(256) void gram_reduce(const float4 *__restrict__ partial, int tri, int chunks,
                                                    bool first, bool last, double4 *__restrict__ g64, int64_t ldg,
                                                    const double *__restrict__ diag, int least,
@@ -609,6 +621,7 @@ __global__ __launch_bounds__(256) void gram_fallback(const double *__restrict__ 
 
 struct GramPlan {
     bool use = false;
+    bool carried = false;  // more passes than kGrCarry: fp64 sums between them
     int64_t nt = 0, tri = 0, ldg = 0;
     int64_t chunk = 0, chunks = 0, pass_chunks = 0;
     size_t partial_offset = 0, g64_offset = 0, plane_offset = 0, plane_bytes = 0;
@@ -620,9 +633,9 @@ struct GramPlan {
 // partials at the rates measured, and a fixed cost; within 7% from 845 us to
 // 6.8 ms) is at most 0.6 of the direct product's: n^2 T against 4 n m T, so
 // from about m = 0.7 n up for long calibration sets (262144 x 4096 against
-// 14336 rows: 5.8 ms, direct 45.8 ms).  The 0.6 leaves the direct product of
+// 14336 rows: 5.6 ms, direct 45.8 ms).  The 0.6 leaves the direct product of
 // the 38% of rows that may have to be listed (kGrCancel) within about the
-// direct route's time (such X, with 14336 rows 24.5 ms against 46.1; 65536 x
+// direct route's time (such X, with 14336 rows 24.3 ms against 46.1; 65536 x
 // 2048 with 2048 rows, near the line, 0.50 ms or 0.96 against 0.85).
 GramPlan gram_plan(int64_t tokens, int64_t in, int64_t out, int64_t ldd, int64_t rows_pad, size_t base) {
     GramPlan p;
@@ -660,15 +673,15 @@ GramPlan gram_plan(int64_t tokens, int64_t in, int64_t out, int64_t ldd, int64_t
     const double T = (double)tokens, m = (double)rows_pad, n = (double)ldd;
     const double direct = 4.0 * T * n * m / 1.3e15;
     const double units = (double)p.chunks * (double)p.tri;
-    const double carried = p.pass_chunks < p.chunks ? (double)((p.chunks + p.pass_chunks - 1) / p.pass_chunks) : 0.0;
+    p.carried = (p.chunks + p.pass_chunks - 1) / p.pass_chunks > kGrCarry;
     const double gram = 131072.0 * (double)p.tri * T / 1.2e15 + 6.0 * m * 65536.0 * (double)p.tri / 1.1e15 +
-                        (units * 32.0 + carried * (double)p.tri * 64.0) * kGrUnitVecs / 7e12 + 100e-6;
+                        units * kGrUnitVecs * 32.0 / 7e12 + 100e-6;
     if (gram > 0.6 * direct) return p;
     p.use = true;
     p.plane_bytes = (size_t)p.ldg * (size_t)p.ldg * 2;
     p.partial_offset = round_up(base, 256);
     p.g64_offset = p.partial_offset + (size_t)(p.pass_chunks * p.tri) * kGrUnitVecs * 16;
-    p.plane_offset = p.g64_offset + (p.pass_chunks < p.chunks ? (size_t)p.tri * kGrUnitVecs * 32 : 0);
+    p.plane_offset = p.g64_offset + (p.carried ? (size_t)p.tri * kGrUnitVecs * 32 : 0);
     p.diag_offset = p.plane_offset + 2 * p.plane_bytes;
     p.scale_offset = p.diag_offset + (size_t)p.ldg * 8;
     p.info_offset = p.scale_offset + (size_t)p.ldg * 4;

@@ -91,31 +91,34 @@ REL_TOL = 1e-4
 # fp64 but for the chains of G, at most 128 steps of 16 tokens that round to
 # 2^-24 of their sum each; in random order about sqrt(128) / 2 of that, 3.4e-7,
 # and what many entries add to a row averages out.  The planes hold 22 bits,
-# 2.4e-7.  Measured 2e-7 to 5e-7; four times the sum of the two.
+# 2.4e-7.  Four times the sum of the two; measured 2e-7 to 6e-7, and 1.4e-6 over
+# 24577 rows of 16384 columns, whose product with G adds up in 3072 fp32 steps.
 GRAM_TOL = 2.4e-6
 
 
-def _passes_over_partials(hs, T, n, m):
-    """Whether the partials of one pass cover fewer tokens than T: their part
-    of the workspace, 256 KB to a tile and chunk of at most 2048 tokens (the
-    chain length that repeated tokens need, tested below), and 512 KB to a tile
-    for the sums carried between passes."""
+def _chunks_held(hs, T, n, m):
+    """Chunks whose partials the workspace holds (256 KB to a tile and chunk),
+    and two more where fp64 sums of the tiles are carried between passes.
+    Chunks have at most 2048 tokens, the chain length that repeated tokens
+    need (tested below): so T beyond as many takes several passes."""
     nt = -(-n // 256)
     ldg, tri = nt * 256, nt * (nt + 1) // 2
     rest = 2 * ldg * ldg * 2 + 12 * ldg + 16 * m + 8 * nt * m + 256 + 4 * m
     least = hs._lib.hscale_output_error_least_workspace_bytes(T, n, m)
-    chunks = (hs.output_error_workspace_bytes(T, n, m) - rest - least) // (tri << 18)
-    return (chunks - 2) * 2048 < T
+    return (hs.output_error_workspace_bytes(T, n, m) - rest - least) // (tri << 18)
 
 
 # One column tile and a ragged one; a last tile of 16 columns; ragged tokens
 # and rows; more partial tiles than one pass holds (136 and 528 tiles to a
-# chunk), the last pass shorter and its last chunk ragged.
+# chunk), the last pass shorter and its last chunk ragged; and more passes than
+# add up in fp32 (2080 tiles, 17 passes of 2 chunks).
 @pytest.mark.parametrize("T,n,m", [(400001, 240, 4097), (120000, 528, 3000), (70007, 1040, 4100),
-                                   (65536, 2048, 2048), (8192 * 34 + 77, 4096, 4096), (2048 * 34 + 77, 8192, 8192)])
+                                   (65536, 2048, 2048), (8192 * 34 + 77, 4096, 4096), (2048 * 34 + 77, 8192, 8192),
+                                   (2048 * 33 + 77, 16384, 24577)])
 def test_gram_route_matches_float64_and_the_direct_route(hs, T, n, m):
     X, W = _case(T, n, m, seed=T + n + m)
-    assert _passes_over_partials(hs, T, n, m) == (n >= 4096)
+    held = _chunks_held(hs, T, n, m)
+    assert (held * 2048 < T) == (n >= 4096) and (n < 16384 or held == 4)
     s_g, codes, packed = _stored(hs, W)
     codes[m // 2].zero_()  # a zero scale: dW = W
     gram, plain = _both(hs, X, W, s_g, codes, packed)

@@ -154,7 +154,8 @@ def test_split_search_lines(hs, groups, down, up):
     _check(W, h, s_g, down, up, codes, packed, "rtn", f"split lines {groups}")
     st = hs.search_stats(W, h, s_g, down, up)
     assert torch.equal(st["scale_codes"], codes) and torch.equal(st["packed_e2m1"], packed)
-    rep = parity.compare_stats(tensor_bits(W), h.cpu().numpy(), s_g, down, up, {k: v.cpu().numpy() for k, v in st.items()})
+    rep = parity.compare_stats(tensor_bits(W), h.cpu().numpy(), s_g, down, up,
+                               {k: v.cpu().numpy() for k, v in st.items()})
     assert rep["ok"], {k: v for k, v in rep.items() if k != "search"}
 
 
