@@ -1002,8 +1002,8 @@ int hscale_shift_summary(const int8_t *shift, const float *err_best, const float
                                err_best, err_init, groups, down, up, part, cnt);
         if (launch_status() != HSCALE_OK) return HSCALE_ERR_HIP;
     }
-    hipLaunchKernelGGL(shift_summary_final, dim3((unsigned)K), dim3(kSumThreads), 0, stream, part, cnt, blocks, K, count,
-                       sum_init, sum_best, sum_rel);
+    hipLaunchKernelGGL(shift_summary_final, dim3((unsigned)K), dim3(kSumThreads), 0, stream, part, cnt, blocks, K,
+                       count, sum_init, sum_best, sum_rel);
     return launch_status();
 }
 

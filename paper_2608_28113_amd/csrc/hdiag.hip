@@ -10,7 +10,8 @@
 //                  caller's workspace.
 //   hdiag_small    the whole sum of few tokens (hdiag_one_launch) in one launch.
 //   hdiag_tree     fixed-order fp64 sum of the slice partials, one fp32 h per
-//                  column (4, 16 or 64 lanes per column by slice count).  No atomics: results are bit-identical run to run.
+//                  column (4, 16 or 64 lanes per column by slice count).  No
+//                  atomics: results are bit-identical run to run.
 
 #include "common.h"
 
@@ -214,7 +215,8 @@ __global__ __launch_bounds__(kHdThreads) void hdiag_partial(const u32x4 *__restr
 // from one block per CU.
 // Measured: 128 x 512 3.5 us, in two launches 6.3; 512 x 4096 5.6 and 10.3;
 // 1024 x 4096 7.0 and 10.5; at 2048 tokens its two batches of loads one after
-// the other take 10.7 us against 8.6 in two launches of more blocks.
+// the other take 10.7 us against 8.6 in two launches of more blocks.  Where it
+// ends by columns: hdiag_one_launch.
 template <bool kAccumulate, int kThreads, int kRowLanes>
 __global__ __launch_bounds__(kThreads) void hdiag_small(const u32x4 *__restrict__ X, int tokens, int64_t in,
                                                         float *__restrict__ h, double *__restrict__ h64) {

@@ -609,7 +609,9 @@ template <bool kStats>
 void launch_split(int init_mode, dim3 grid, hipStream_t stream, const SearchArgs &a) {
     const dim3 block(kSearchThreads);
     switch (init_mode) {
-        case kInitMaxAbs: hipLaunchKernelGGL((search_split_kernel<kInitMaxAbs, kStats>), grid, block, 0, stream, a); break;
+        case kInitMaxAbs:
+            hipLaunchKernelGGL((search_split_kernel<kInitMaxAbs, kStats>), grid, block, 0, stream, a);
+            break;
         case kInitFourOverSix:
             hipLaunchKernelGGL((search_split_kernel<kInitFourOverSix, kStats>), grid, block, 0, stream, a);
             break;

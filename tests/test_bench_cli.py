@@ -62,6 +62,14 @@ def test_committed_diagnostics_profile_is_current():
     assert t is not None, "profiles/output_error_down_proj.json is absent or older than the kernel sources"
 
 
+def test_committed_routes_profile_is_current():
+    """profiles/output_error_routes.md (the kernels that the down_proj summary
+    does not reach) names the current output-error sources."""
+    import bench
+    text = (ROOT / "profiles" / "output_error_routes.md").read_text()
+    assert f"at collection: `{bench.source_hash(bench.DIAG_SOURCES)}`" in text, "re-collect the routes profile"
+
+
 def test_committed_ceilings_profile_is_current():
     """profiles/ceilings_down_proj.md (the probe kernels' trace beside the
     bench's timings) names the source hash of csrc/probes.hip it was taken

@@ -72,3 +72,42 @@ def test_hdiag_search_and_output_error_replay_in_a_graph(hs):
         # eager work between replays
         X.mul_(1.0)
         torch.cuda.synchronize()
+
+
+def test_output_error_over_several_passes_replays_in_a_graph(hs):
+    """The route through X^T X, with several passes over its partials and half
+    of the rows listed for the direct product: captured, each replay adds the
+    same sums again."""
+    from tests.test_gpu_gram import _chunks_held, _opposed, _stored
+    T, n, m = 69709, 4096, 4096
+    X, W = _opposed(T, n, m, 0.1)
+    s_g, codes, packed = _stored(hs, W)
+    need = hs.output_error_workspace_bytes(T, n, m)
+    assert 2 <= _chunks_held(hs, T, n, m) < T // 2048  # this route, in several passes
+    ws = torch.empty(need, dtype=torch.uint8, device=DEV)
+    row = torch.zeros(m, dtype=torch.float64, device=DEV)
+    hs.output_error(X, W, s_g, codes, packed, row_err=row, workspace=ws)
+    torch.cuda.synchronize()
+    ref = row.clone()
+
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        hs.output_error(X, W, s_g, codes, packed, row_err=row, workspace=ws)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    assert torch.equal(row, ref + ref)
+
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        hs.output_error(X, W, s_g, codes, packed, row_err=row, workspace=ws)
+    for i in range(3):
+        row.zero_()
+        ws.fill_(0xFF)  # whatever earlier passes left: nothing of it may be read
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(row, ref), f"replay {i}"
+        again = hs.output_error(X, W, s_g, codes, packed)
+        torch.cuda.synchronize()
+        assert torch.equal(again, ref), f"eager {i}"
