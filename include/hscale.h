@@ -378,16 +378,17 @@ size_t hscale_output_error_least_workspace_bytes(int64_t tokens, int64_t in,
  * (a rule on the sizes) and the workspace holds what
  * hscale_output_error_workspace_bytes says, the same sums come from
  * G = X^T X instead: exact bf16 products accumulated in fp32 over at most
- * 2048 tokens, those sums in fp32 over at most 16 passes, the rest in fp64; G's diagonal applied in fp64, the rest as 22-bit
- * scaled values; rows whose terms cancel to below 1/4 of their diagonal
- * part, or leave fp32's range, are computed by the direct product.  Both are
- * bitwise reproducible for a given problem and workspace size; the second is
- * the closer to Eq. 3 (about 1e-7 of the result against 4e-6, and no further
- * than the direct product where the tokens repeat).  It takes 8 to 1.7
- * times less time, by the sizes; where one direction that many channels share
- * makes up X^T X, about 38% of the rows cancel that far and take the direct
- * product on top, which brings the smaller of these calls back to about the
- * direct route's time.
+ * 2048 tokens, those sums in fp32 over at most 16 passes and the rest in
+ * fp64; G's diagonal applied in fp64, the rest as 22-bit scaled values; rows
+ * whose terms cancel to below 1/4 of their diagonal part, or leave fp32's
+ * range, are computed by the direct product.  Both are bitwise reproducible
+ * for a given problem and workspace size; the second is the closer to Eq. 3
+ * (about 1e-7 of the result against 4e-6, and no further than the direct
+ * product where the tokens repeat).  It takes 8 to 1.7 times less time, by
+ * the sizes; where one direction that many channels share makes up X^T X,
+ * about 38% of the rows cancel that far and take the direct product on top,
+ * which brings the smaller of these calls back to about the direct route's
+ * time.
  *
  * X            bf16 [tokens, in], 16-byte aligned
  * W            bf16 [out, in], 16-byte aligned

@@ -31,7 +31,7 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 // gram_kernel: a 256 x 256 tile of G per block, 8 waves of 128 x 64, two per
 // SIMD.  The matrix cores bound it, at the clock that the power leaves, and the
 // partials at the ends of its short chains: 262144 tokens of 4096 columns take
-// 4.6 ms in chunks of 2048 tokens (MFMA busy 0.57 at 1.7 GHz), 3.7 ms = 1.27
+// 4.7 ms in chunks of 2048 tokens (MFMA busy 0.56 at 1.75 GHz), 3.7 ms = 1.27
 // PFLOP/s issued in chunks of 17500 (0.75 at 1.6 GHz).  What mattered: reads of
 // the next 16-token step interleaved with the MFMAs of the current one, two
 // reads to an MFMA (4.3 ms against 3.7 without); 128 x 128 per wave at one wave
