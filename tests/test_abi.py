@@ -60,7 +60,7 @@ def test_workspace_bytes(L):
 def test_hdiag_workspace_serves_shorter_batches(L):
     """The size covers slices of at least 256 tokens over the resident grid,
     whatever plan is taken, so that a buffer sized for a full batch is enough
-    for every shorter one of at least as many columns' partials."""
+    for a shorter one."""
     def coarse(T, n):
         slices = max(1, min(1792 // -(-n // 512), -(-T // 256)))
         return -(-T // -(-T // slices)) * n * 8
