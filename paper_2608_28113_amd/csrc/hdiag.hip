@@ -43,14 +43,15 @@ constexpr int kHdTargetBlocks = 1792;
 constexpr int64_t kHdSmallTokens = 1024;
 constexpr int64_t kHdFewTokens = 256;
 // Above kHdFewTokens its blocks of 64 columns and 1024 threads read 128 bytes
-// of a row each, which pays while every CU has at most one (257 to 1024
-// tokens x 16384 columns 5.1 to 7.7 us, in two launches 7.4 to 11.0), and with
-// two in the middle of the range (28672 columns: 320 tokens 8.0 against 8.4,
-// 512 8.3 against 10.9, 900 11.2 against 11.4, but 257 7.8 both, 1024 12.4
-// against 12.2); beyond that it loses (57344 columns: 257 tokens 13.0 against
-// 8.4, 512 14.2 against 12.3, 1024 23.2 against 20.3).
+// of a row each, which pays while a CU has at most one (257 to 1024 tokens x
+// 16384 columns 5.1 to 7.7 us, in two launches 7.4 to 11.0).  With two it takes
+// as long as two launches at 257 tokens (28672 columns: 7.8 us and 7.7), where
+// a launch less is 2 us less for the host, and less up to 896 (512 tokens 8.3
+// and 10.9, 896 11.2 both); 1024 tokens take longer (accumulated batch by
+// batch, 16400 columns 12.9 against 11.9, 32768 15.5 against 14.9).  With more
+// it loses (57344 columns: 257 tokens 13.0 against 8.4, 512 14.2 against 12.3).
 constexpr int64_t kHdSmallCols = 16384;
-constexpr int64_t kHdTwiceMinTokens = 320, kHdTwiceMaxTokens = 896;
+constexpr int64_t kHdTwiceTokens = 896;
 // Up to kHdFewTokens a block reads 256 bytes of 16 rows at once, which leaves
 // lanes idle below 16 rows: no loss while launches bound the call (262144
 // columns: 1 token 5.7 us, in two launches 6.6; 16 tokens 6.7 and 6.9), but
@@ -114,8 +115,7 @@ HdiagPlan hdiag_plan(int64_t tokens, int64_t in, bool coarse) {
 // Whether hdiag_small takes it.
 bool hdiag_one_launch(int64_t tokens, int64_t in) {
     if (tokens <= kHdFewTokens) return in <= kHdFewCols || tokens >= kHdFewMinTokens;
-    return (tokens <= kHdSmallTokens && in <= kHdSmallCols) ||
-           (tokens >= kHdTwiceMinTokens && tokens <= kHdTwiceMaxTokens && in <= 2 * kHdSmallCols);
+    return (tokens <= kHdSmallTokens && in <= kHdSmallCols) || (tokens <= kHdTwiceTokens && in <= 2 * kHdSmallCols);
 }
 
 size_t hdiag_bytes(const HdiagPlan &p, int64_t in) { return (size_t)p.slices * (size_t)in * sizeof(double); }
