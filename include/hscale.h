@@ -384,11 +384,12 @@ size_t hscale_output_error_least_workspace_bytes(int64_t tokens, int64_t in,
  * range, are computed by the direct product.  Both are bitwise reproducible
  * for a given problem and workspace size; the second is the closer to Eq. 3
  * (about 1e-7 of the result against 4e-6, and no further than the direct
- * product where the tokens repeat).  It takes 8 to 1.7 times less time, by
+ * product where the tokens repeat).  It takes 8 to 1.4 times less time, by
  * the sizes; where one direction that many channels share makes up X^T X,
- * about 38% of the rows cancel that far and take the direct product on top,
- * which brings the smaller of these calls back to about the direct route's
- * time.
+ * about 38% of the rows cancel that far and take the direct product on top:
+ * the largest of these calls then still gain, the smallest take up to a
+ * quarter longer than the direct route.  A workspace of the least size keeps
+ * a call on the direct route.
  *
  * X            bf16 [tokens, in], 16-byte aligned
  * W            bf16 [out, in], 16-byte aligned

@@ -783,37 +783,40 @@ __global__ __launch_bounds__(64 * kWM * kWN, 2) void lfull_pipe_kernel(const LfA
 // The tiles, and what a stage of 32 columns costs: the time of a block that
 // has a CU for itself (LDS reads, waits and barriers), and the rate with all
 // CUs busy, where LDS traffic per MFMA and the clock that the power leaves
-// decide.  Measured with both on 64 to 65536 tokens x 64 to 14336 rows x 1024
-// to 14336 columns; the estimate below is within 15% there and picks the
-// fastest or one within 3%.
+// decide; and what a round of blocks costs beside its stages (first loads and
+// column sums; the smaller two share a CU in pairs), which decides where
+// columns are few: 50290 tokens x 1149 rows x 80 columns 34.1 us, with 256-token
+// tiles, which their three stages alone favour, 36.8.  Measured with all on 64
+// to 65536 tokens x 17 to 14336 rows x 64 to 14336 columns; the estimate below
+// is within 15% there and picks the fastest or one within 3%.
 enum LfTile : int { kLfWide, kLfMid, kLfNarrow, kLfSmall, kLfTiny };
 struct LfTileInfo {
     int64_t tokens, rows;
-    double stage_us, pflops;
+    double stage_us, pflops, round_us;
 };
 constexpr LfTileInfo kLfTiles[] = {
-    {kLfBM, kLfBN, 1.60, 1.40},  // 65536 x 4096 x 14336: 11.0 ms, mid 11.2, narrow 14.7
-    {256, 256, 1.15, 1.365},     // 4096 x 4096 x 4096: 202 us, wide 225, narrow 234
-    {128, 256, 0.70, 1.15},      // 2048 x 4096 x 4096: 119 us, mid 142, small 136
-    {128, 128, 0.44, 1.00},      // 1024 x 2048 x 2048: 32 us, narrow 48, mid 77, tiny 30
-    {64, 128, 0.36, 0.72},       // 512 x 4096 x 4096: 51 us, small 57, narrow 89; 256 x 512 x 2048: 23, 30, 44
+    {kLfBM, kLfBN, 1.60, 1.40, 1.5},  // 65536 x 4096 x 14336: 11.0 ms, mid 11.2, narrow 14.7
+    {256, 256, 1.15, 1.365, 1.5},     // 4096 x 4096 x 4096: 202 us, wide 225, narrow 234
+    {128, 256, 0.70, 1.15, 1.5},      // 2048 x 4096 x 4096: 119 us, mid 142, small 136
+    {128, 128, 0.44, 1.00, 0.75},     // 1024 x 2048 x 2048: 32 us, narrow 48, mid 77, tiny 30
+    {64, 128, 0.36, 0.72, 0.75},      // 512 x 4096 x 4096: 51 us, small 57, narrow 89; 256 x 512 x 2048: 23, 30, 44
 };
 constexpr int kLfTileCount = sizeof(kLfTiles) / sizeof(kLfTiles[0]);
 
-// The tile with the least estimated time: full rounds of 256 blocks, then the
-// rest.
-LfTile lfull_tile(int64_t tokens, int64_t out) {
+// The tile with the least estimated time, and that time: full rounds of 256
+// blocks, then the rest.
+LfTile lfull_tile(int64_t tokens, int64_t out, int64_t stages, double &us) {
     int best = kLfWide;
-    double least = 0.0;
     for (int k = 0; k < kLfTileCount; ++k) {
         const LfTileInfo &t = kLfTiles[k];
         const int64_t blocks = ((tokens + t.tokens - 1) / t.tokens) * ((out + t.rows - 1) / t.rows);
         const double work = (double)(4 * t.tokens * t.rows * kLfBK) / (t.pflops * 1e9);  // us of a block's share
         auto round = [&](int64_t b) { return (double)b * work > t.stage_us ? (double)b * work : t.stage_us; };
-        const double est = (double)(blocks / 256) * round(256) + (blocks % 256 ? round(blocks % 256) : 0.0);
-        if (k == 0 || est < least) {
+        const double stage = (double)(blocks / 256) * round(256) + (blocks % 256 ? round(blocks % 256) : 0.0);
+        const double est = (double)stages * stage + (double)((blocks + 255) / 256) * t.round_us;
+        if (k == 0 || est < us) {
             best = k;
-            least = est;
+            us = est;
         }
     }
     return (LfTile)best;
@@ -833,6 +836,7 @@ void launch_tiles(LfTile tile, int64_t token_tiles, hipStream_t stream, const Lf
 struct LfPlan {
     int64_t ldd = 0, rows_pad = 0, ntiles = 0;  // ntiles: of kLfBN rows
     LfTile tile = kLfWide;
+    double product_us = 0.0;  // estimated
     int64_t tile_tokens = 0, row_tiles = 0;  // of the chosen tile
     int64_t tiles_per_pass = 0;              // token tiles of a pass
     int64_t wide_per_pass = 0;               // the same with kLfWide tiles
@@ -846,7 +850,7 @@ LfPlan lfull_plan(int64_t tokens, int64_t in, int64_t out) {
     p.ldd = (in + kLfBK - 1) / kLfBK * kLfBK;
     p.rows_pad = (out + kLfBN - 1) / kLfBN * kLfBN;
     p.ntiles = p.rows_pad / kLfBN;
-    p.tile = lfull_tile(tokens, out);
+    p.tile = lfull_tile(tokens, out, p.ldd / kLfBK, p.product_us);
     p.tile_tokens = kLfTiles[p.tile].tokens;
     p.row_tiles = (out + kLfTiles[p.tile].rows - 1) / kLfTiles[p.tile].rows;
     // A pass launches tiles_per_pass x row tiles blocks: at most
@@ -1016,7 +1020,7 @@ size_t hscale_output_error_least_workspace_bytes(int64_t tokens, int64_t in, int
 size_t hscale_output_error_workspace_bytes(int64_t tokens, int64_t in, int64_t out) {
     if (in % kGroup != 0 || in > kLfMaxIn || (in > 0 && out > kMaxGroups / (in / kGroup))) return 0;
     const LfPlan p = lfull_plan(tokens, in, out);
-    const GramPlan g = gram_plan(tokens, in, out, p.ldd, p.rows_pad, p.bytes);
+    const GramPlan g = gram_plan(tokens, in, out, p);
     return g.use ? g.bytes : p.bytes;
 }
 
@@ -1053,7 +1057,7 @@ int hscale_output_error(const void *X, int64_t tokens, int64_t in, const void *W
     // buffer: the partials of the direct product's smaller tiles, and the Gram
     // route.
     const bool small_tiles = workspace_bytes >= p.bytes && !hits(p.bytes);
-    const GramPlan gp = gram_plan(tokens, in, out, p.ldd, p.rows_pad, p.bytes);
+    const GramPlan gp = gram_plan(tokens, in, out, p);
     const bool gram = gp.use && workspace_bytes >= gp.bytes && !hits(gp.bytes);
 
     uint8_t *ws = static_cast<uint8_t *>(workspace);

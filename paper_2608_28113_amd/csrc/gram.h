@@ -629,16 +629,17 @@ struct GramPlan {
     size_t diag_offset = 0, scale_offset = 0, info_offset = 0, part_offset = 0, list_offset = 0, bytes = 0;
 };
 
-// The Gram route's plan, behind the direct route's workspace of `base` bytes.
-// It is used where its estimated time (matrix-core flops and traffic of the
-// partials at the rates measured, and a fixed cost; within 7% from 845 us to
-// 6.8 ms) is at most 0.6 of the direct product's: n^2 T against 4 n m T, so
-// from about m = 0.7 n up for long calibration sets (262144 x 4096 against
-// 14336 rows: 5.6 ms, direct 45.8 ms).  The 0.6 leaves the direct product of
-// the 38% of rows that may have to be listed (kGrCancel) within about the
-// direct route's time (such X, with 14336 rows 24.3 ms against 46.1; 65536 x
-// 2048 with 2048 rows, near the line, 0.50 ms or 0.96 against 0.85).
-GramPlan gram_plan(int64_t tokens, int64_t in, int64_t out, int64_t ldd, int64_t rows_pad, size_t base) {
+// The Gram route's plan, behind the direct route's workspace.  It is used where
+// its estimated time (matrix-core flops and traffic of the partials at the
+// rates measured, and a fixed cost; within 15% from 125 us to 37 ms) is at most
+// 0.7 of the direct product's: n^2 T against 4 n m T, so from about m = 0.6 n up
+// for long calibration sets (262144 x 4096 against 14336 rows: 5.6 ms, direct
+// 44.3 ms; 8504 x 2992 against 9357 rows 0.48 ms, direct 0.89).  Where 38% of
+// the rows have to be listed (kGrCancel) the smaller calls and those near the
+// line lose instead (65536 x 2048 with 2048 rows 0.50 ms or 0.99, direct 0.87;
+// 11750 x 2672 with 5937 rows 0.40 or 0.78, direct 0.62); larger ones still
+// gain (with 14336 rows above 23.4 ms, direct 44).
+GramPlan gram_plan(int64_t tokens, int64_t in, int64_t out, const LfPlan &d) {
     GramPlan p;
     if (tokens <= 0 || in <= 0 || out <= 0) return p;
     p.nt = (in + kGrTile - 1) / kGrTile;
@@ -671,16 +672,15 @@ GramPlan gram_plan(int64_t tokens, int64_t in, int64_t out, int64_t ldd, int64_t
     p.chunks = (tokens + p.chunk - 1) / p.chunk;
     p.pass_chunks = per_pass(p.chunks);
 
-    const double T = (double)tokens, m = (double)rows_pad, n = (double)ldd;
-    const double direct = 4.0 * T * n * m / 1.3e15;
+    const double T = (double)tokens, m = (double)d.rows_pad;
     const double units = (double)p.chunks * (double)p.tri;
     p.carried = (p.chunks + p.pass_chunks - 1) / p.pass_chunks > kGrCarry;
     const double gram = 131072.0 * (double)p.tri * T / 1.2e15 + 6.0 * m * 65536.0 * (double)p.tri / 1.1e15 +
-                        units * kGrUnitVecs * 32.0 / 7e12 + 100e-6;
-    if (gram > 0.6 * direct) return p;
+                        units * kGrUnitVecs * 32.0 / 7e12 + 80e-6;
+    if (gram > 0.7e-6 * d.product_us) return p;
     p.use = true;
     p.plane_bytes = (size_t)p.ldg * (size_t)p.ldg * 2;
-    p.partial_offset = round_up(base, 256);
+    p.partial_offset = round_up(d.bytes, 256);
     p.g64_offset = p.partial_offset + (size_t)(p.pass_chunks * p.tri) * kGrUnitVecs * 16;
     p.plane_offset = p.g64_offset + (p.carried ? (size_t)p.tri * kGrUnitVecs * 32 : 0);
     p.diag_offset = p.plane_offset + 2 * p.plane_bytes;

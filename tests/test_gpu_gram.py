@@ -217,11 +217,13 @@ def test_squares_outside_fp32_go_direct(hs, scale):
 
 
 # The direct route's tiles, tokens x rows: 64 x 128 (the first five cases, of
-# 1, 1, 2, 3 and 33 stages), 128 x 128 (two), 128 x 256 (two), 256 x 256 (two)
-# and 384 x 256 (the last); edges, ragged rows and columns, more than a round.
+# 1, 1, 2, 3 and 33 stages), 128 x 128 (two), 128 x 256 (three), 256 x 256
+# (three) and 384 x 256 (the last); edges, ragged rows and columns, more than a
+# round.
 @pytest.mark.parametrize("T,n,m", [(1, 16, 1), (127, 32, 255), (129, 48, 257), (65, 80, 129), (385, 1040, 513),
-                                   (2945, 48, 1025), (3000, 96, 700), (2050, 16, 3900), (6500, 208, 700),
-                                   (2049, 528, 4100), (4096, 256, 4096), (5000, 80, 4096)])
+                                   (2945, 48, 1025), (3000, 96, 700), (1801, 16, 3001), (1300, 80, 3900),
+                                   (6500, 208, 700), (2050, 16, 3900), (2049, 528, 4100), (4096, 256, 4096),
+                                   (5000, 80, 4096)])
 def test_direct_tiles_and_smaller_workspaces(hs, T, n, m):
     X, W = _case(T, n, m, seed=T + m)
     s_g, codes, packed = _stored(hs, W)
